@@ -24,9 +24,9 @@ sys.path.insert(0, ROOT)
 PEAK_HBM_GBPS = 8000.0  # MI355X HBM3E, AMD published peak
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "fused_sync_resnet50_counters.txt")
 # sources whose change invalidates the committed counter figures: the kernels,
-# their launch interface and the host code that picks the tile order and grid
+# their launch interface, the cut into launches and the host code that picks the grid
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2104_05588_amd", "csrc", f)
-                  for f in ("daso_kernels.hip", "daso_launch.h", "daso_api.hip")]
+                  for f in ("daso_kernels.hip", "daso_launch.h", "daso_plan.h", "daso_api.hip")]
 PROBE_LIB = os.path.join(ROOT, "paper_2104_05588_amd", "libdaso_ceiling.so")
 
 

@@ -55,35 +55,25 @@
  *    included), so empty buffers may be NULL.
  *  - On an argument error (DASO_EINVAL, DASO_EALIGN, DASO_EALIAS) nothing is
  *    launched and the buffers are untouched; daso_status_string names the
- *    status.  A call may queue more than one kernel: one per 64 buckets of its
- *    table, and a statistics pass after each fused launch with statistics
- *    (except an eager launch of at most 64 tiles of daso_fused_sync_step,
- *    whose last workgroup sums its statistics itself; a call being captured
- *    into a graph keeps the pass, as daso_fused_sync_step_noalloc always
- *    does), and one zeroing kernel on the first eager call that uses a new
- *    statistics workspace.  If
+ *    status.  A call may queue more than one kernel: one per 128 buckets of its
+ *    table (without statistics, of its runs of buckets of one staleness), one
+ *    statistics pass after them (except an eager call of
+ *    daso_fused_sync_step over at most 128 slices of 1024 parameters, whose last workgroup sums
+ *    its statistics itself; a call being captured into a graph keeps the
+ *    pass, as daso_fused_sync_step_noalloc always does), and one zeroing kernel
+ *    on the first eager call that uses a new statistics workspace.  If
  *    queueing one of them fails (DASO_EHIP), the kernels queued before it still
  *    run: the outputs (params, momentum, wire, grad_avg, stats) of the buckets
  *    they cover may then already be updated, the others are untouched.
- *  - Launch shape: the fused step hands each XCD runs of consecutive tiles
- *    (about 64 blocks of 8 runs per launch from 9 streams) and, from 10
- *    streams, lets at most 2 workgroups share a CU; both were measured best on
- *    MI355X (daso_fused_launch_config reports them).  For each shape of a
- *    single launch (up to 64 buckets), the 6 calls of daso_fused_sync_step
- *    after its first alternate between those runs and plain tile order,
- *    timed with events on the call's stream that later calls poll (never wait
- *    on); once all of them have completed (samples may be taken on different
- *    streams), plain order is kept for the shape if it was at least 1% faster,
- *    the runs otherwise.
- *    Captured calls take no samples, and polling is skipped while a HIP error
- *    is pending on the calling thread, so that error stays for the caller.
- *    The environment variables DASO_FUSED_RUN_ELEMS (elements per run, 0 =
- *    plain order; no sampling), DASO_FUSED_WG_PER_CU (0 = no cap) and
- *    DASO_FUSED_TUNE (0 = no sampling), read once per process, replace them to
- *    reproduce the measurements.  None of this ever changes a result.
+ *  - Launch shape: a wavefront takes 256 consecutive parameters, and neighbouring
+ *    ones are dealt to the XCDs in turn; workgroups hold LDS that they do not use, so
+ *    that only as many share a CU as have about 60 to 100 KB of loads in
+ *    flight (measured best on MI355X).  The environment variable
+ *    DASO_FUSED_WG_PER_CU (0 = no cap), read once per process, replaces the count
+ *    for the fused step.  It never changes a result.
  *  - Calls may be made from several host threads.  Fused steps with statistics
- *    share one small per-(device, stream) workspace (24 bytes per tile of 1024
- *    or 2048 parameters, plus a 260-byte table of bucket ranges) that the
+ *    share one small per-(device, stream) workspace (24 bytes per 1024
+ *    parameters, plus 216 to 408 bytes per bucket) that the
  *    library allocates on first use (at least 1 MiB), replaces by a larger one
  *    when a larger call needs it, and never frees before the process ends;
  *    calls on one stream are ordered by that stream, and threads may share a
@@ -215,33 +205,32 @@ int daso_fused_sync_step(const daso_sync_args* args, hipStream_t stream);
 /* For callers that cannot allocate device memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): daso_fused_sync_step
  * with the same arguments, results and rules, except that the statistics
- * scratch (a 256-byte counter, 24 bytes per tile of 1024 or 2048 parameters and
- * a 260-byte table, per launch of up to 64 buckets) lives in a fixed array of
- * DASO_NOALLOC_SCRATCH_BYTES in device memory instead of an allocated
- * workspace.  The call never allocates or frees memory.  Every GPU the library
- * runs on holds its own copy of that array until the process ends; the first
+ * scratch lives in a fixed array in device memory instead of an allocated
+ * workspace.  The call never allocates or frees device memory.  Every GPU the library
+ * runs on holds its own copy of that array (about 32 MiB) until the process ends; the first
  * call on a device looks up its address there (that device must be current, as
  * for every call).  All calls of this entry point on one GPU share the array and
  * each leaves its contents behind: calls queued on one stream are ordered by it
  * (host threads may share the stream), but calls on different streams of the
  * same GPU that may run at the same time race on the array and can give wrong
- * statistics; the other outputs are never affected.  A call whose statistics
- * need more than the array holds (more than 699,029 tiles in one launch: at
+ * statistics; the other outputs are never affected.  The limit is stated in the tiles of
+ * daso_fused_launch_config: a call needs 256 bytes, 24 per tile and 260, for
+ * the largest number of tiles of 64 consecutive buckets of its table, and one
+ * that needs more than DASO_NOALLOC_SCRATCH_BYTES (more than 699,029 tiles: at
  * least about 715 million parameters) returns DASO_ENOSPACE and launches
  * nothing.  Without statistics (stats == NULL) no scratch is used. */
 #define DASO_NOALLOC_SCRATCH_BYTES ((size_t)16 << 20)
 int daso_fused_sync_step_noalloc(const daso_sync_args* args, hipStream_t stream);
 
-/* Launch shape of a fused step (host only, no device work), for tools that
- * time the same memory access pattern: daso_fused_sync_step and
- * daso_fused_sync_step_noalloc with these arguments run tiles of tile_elems
- * parameters, one 256-thread workgroup per tile, hand each XCD runs of
- * xcd_run_tiles consecutive tiles (1: plain order), and give each workgroup
- * lds_bytes of LDS (unused by the kernel; it caps how many workgroups share a
- * CU; 0: no cap).  ntiles counts the tiles of the first launch (the first 64
- * buckets).  Once the tile order of the shape has been chosen from its first
- * calls on the current device, xcd_run_tiles reports that choice.  The
- * arguments are checked as the step checks them and the same status is
+/* The tiled plan of a fused step (host only, no device work), for tools that
+ * time a pass over the same streams, and the unit of the limit above: tiles of tile_elems parameters, one
+ * 256-thread workgroup per tile, each XCD taking runs of xcd_run_tiles
+ * consecutive tiles (1: plain order), and lds_bytes of LDS per workgroup (which
+ * caps how many share a CU; 0: no cap).  ntiles counts the tiles of the first
+ * 64 buckets.  The step itself runs in a finer split (see above), which the plan does
+ * not describe.  The environment variables DASO_FUSED_RUN_ELEMS (elements per run,
+ * 0 = plain order) and DASO_FUSED_WG_PER_CU replace the run length and the
+ * cap.  The arguments are checked as the step checks them and the same status is
  * returned; *out is written only on DASO_OK. */
 typedef struct daso_launch_config {
   int64_t tile_elems;

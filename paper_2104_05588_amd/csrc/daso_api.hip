@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <map>
 #include <mutex>
+#include <new>
 #include <utility>
 
 #include "daso_host.h"
@@ -19,8 +20,10 @@ namespace {
 static_assert(sizeof(daso::StepArgs) <= 4096, "StepArgs must fit the 4 KB kernel-argument limit");
 
 using daso::StepArgs;
-using daso::TileBucket;
-using daso::TilePartial;
+using daso::BucketSlots;
+using daso::Group;
+using daso::Ranges;
+using daso::SlicePartial;
 
 // ---------------------------------------------------------------- workspace
 // Per (device, stream): the counter of launches that sum their own statistics
@@ -82,11 +85,14 @@ int zero_counter_once(Workspace& w, hipStream_t stream) {
 // hipGetSymbolAddress (with that device current) and only that address is
 // handed to kernels.  It has the workspace's layout, but its first
 // kStatsCounterBytes are never used: calls through it keep the statistics
-// kernel (see run_groups).  The kernels write every partial and table entry
+// kernel (see launch_groups).  The kernels write every partial and table entry
 // they read later, so the array never needs clearing.
-constexpr size_t kScratchBytes = DASO_NOALLOC_SCRATCH_BYTES;
+// The limit that callers see, DASO_NOALLOC_SCRATCH_BYTES, counts the tiles of the tiled
+// plan, of 2048 or 1024 parameters; the array holds the partials of such a call, which
+// come to one per 1024 parameters, with 64 KB to spare for partials at the edges of
+// buckets.  A call whose buckets need more of those takes more launches.
+constexpr size_t kScratchBytes = 2 * DASO_NOALLOC_SCRATCH_BYTES + (size_t(64) << 10);
 static_assert(kScratchBytes % 256 == 0, "the scratch size is a whole number of 256-byte blocks");
-static_assert(daso::kStatsCounterBytes % 256 == 0, "the partials start on a 256-byte boundary");
 static __device__ __align__(256) uint64_t scratch[kScratchBytes / sizeof(uint64_t)];
 
 constexpr int kMaxDevices = 64;
@@ -110,35 +116,22 @@ int scratch_slot(int dev, ScratchSlot** out) {
 }
 
 // -------------------------------------------------------------- launching
-struct Group {
-  int32_t first;  // index of its first bucket in the caller's table
-  int32_t count;
-  int64_t ntiles;
-};
-
-// The caller's bucket table is cut into launches of at most kLaunchBuckets
-// buckets; group(i) is the launch starting at bucket i (no allocation).
-Group group_at(const daso_bucket* b, int32_t nb, int32_t i, int64_t tile) {
-  Group gr{i, std::min<int32_t>(daso::kLaunchBuckets, nb - i), 0};
-  for (int32_t k = 0; k < gr.count; ++k)
-    gr.ntiles += daso::tiles_of(b[i + k].start, b[i + k].start + b[i + k].numel, tile);
-  return gr;
-}
-
-void fill_group(StepArgs& a, const daso_bucket* b, const Group& gr, int64_t tile) {
-  int64_t t = 0;
-  for (int32_t k = 0; k < gr.count; ++k) {
-    const daso_bucket& s = b[gr.first + k];
-    a.b[k].start = s.start;
-    a.b[k].end = s.start + s.numel;
-    a.b[k].first_tile = static_cast<int32_t>(t);
-    a.b[k].S = s.S;
-    t += daso::tiles_of(s.start, s.start + s.numel, tile);
+// The launch's buckets as kernel arguments.
+void fill_group(StepArgs& a, const Ranges& r, const Group& g, int shift) {
+  for (int32_t k = 0; k < g.count; ++k) {
+    const daso::Range& x = r[g.first + k];
+    const int32_t d = 2 * x.S + a.P;
+    a.start[k] = x.start;
+    a.S[k] = x.S;
+    a.inv[k] = d > 0 ? 1.0f / static_cast<float>(d) : 0.0f;
+    a.out[k] = x.out;
   }
-  a.nb = gr.count;
-  // A launch needs at least one workgroup, even over empty buckets, so that
-  // their statistics are still written (as zeros).
-  a.ntiles = static_cast<int32_t>(std::max<int64_t>(t, 1));
+  a.start[g.count] = g.hi;
+  a.nb = g.count;
+  a.lo = g.lo;
+  a.hi = g.hi;
+  a.sb0 = g.lo >> shift;
+  a.nslices = 8 * daso::superblocks(g.lo, g.hi, shift);
 }
 
 // A non-negative integer from the environment, read once per variable by the
@@ -151,12 +144,10 @@ int64_t env_count(const char* name, int64_t fallback, int64_t max) {
   return (end != e && *end == '\0' && x >= 0 && x <= max) ? static_cast<int64_t>(x) : fallback;
 }
 
-// DASO_FUSED_RUN_ELEMS, when set to a number of elements, replaces the run
-// length of fused launches of kXcdRunFusedStreams streams or more (0: plain
-// order); DASO_FUSED_WG_PER_CU, when set, replaces the workgroups-per-CU cap of
-// fused launches of kCapStreams streams or more (0: no cap).  Neither ever
-// changes a result; they exist to reproduce the measurements behind the
-// defaults.  Each is read once per process.
+// DASO_FUSED_WG_PER_CU, when set, replaces the workgroups per CU of fused
+// launches (0: no cap) and of the tiled plan; DASO_FUSED_RUN_ELEMS, a number of
+// elements, replaces the run length of the tiled plan (0: plain order).  Neither
+// changes a result.  Each is read once per process.
 int64_t fused_run_elems_override() {
   static const int64_t v = env_count("DASO_FUSED_RUN_ELEMS", -1, int64_t(1) << 30);
   return v;
@@ -166,35 +157,54 @@ int64_t fused_cap_override() {
   return v;
 }
 
-// Streams a launch touches (the tile-order and occupancy rules go by it).
-int launch_streams(daso::Mode mode, const StepArgs& a) {
-  if (mode == daso::kModeAvg) return a.g + 1;
-  if (mode == daso::kModeMerge) return a.P + 2 + (a.wire ? 1 : 0);
-  if (mode == daso::kModeFused) return a.g + a.P + 4 + (a.wire ? 1 : 0) + (a.gavg ? 1 : 0);
-  return 2;
-}
-
-// Tiles per XCD run of one launch of `ntiles` tiles of `tile` elements (the
-// rule and its measurements are stated with the constants in daso_launch.h).
-int32_t xcd_run_of(daso::Mode mode, int streams, int64_t ntiles, int64_t tile) {
-  if (mode == daso::kModeFused && streams >= daso::kXcdRunFusedStreams) {
-    const int64_t over = fused_run_elems_override();
-    if (over >= 0) return static_cast<int32_t>(std::max<int64_t>(1, over / tile));
-    int64_t run = 1;
-    while (run * 2 <= ntiles / (8 * daso::kXcdRunBlocksPerLaunch) && run < (int64_t(1) << 20)) run *= 2;
-    return static_cast<int32_t>(run);
-  }
-  if (streams >= daso::kXcdRunManyStreams) return daso::kXcdRunMany;
-  if (streams >= daso::kXcdRunMidStreams) return daso::kXcdRunMid;
-  return 1;
-}
-
-// LDS per workgroup of a launch: the occupancy cap of the fused step.
-int32_t lds_of(daso::Mode mode, int streams) {
-  if (mode != daso::kModeFused) return 0;
+// LDS per workgroup, which caps how many workgroups share a CU.  By the bytes B
+// that an element is read with; the best caps on MI355X, 25.6M (and, but for the
+// fused step, 70.5M) parameters:
+//  - workgroups of one wavefront: 190 / B of them for the fused step, 240 / B for
+//    averages and merges, 5 to 16.  g = 1, P = 0 (B = 12): 87 us at 16, 92 at 8; g = 4, P = 0
+//    (24): 132 at 8, 135 at 12, 145 at 20; g = 4, P = 8 (40): 197 at 5, 200 at 10, 213 at 20;
+//    g = 8, P = 8 (56): 266 at 5, 278 at 10.  Averages of 3, 4 and 8 gradients: best
+//    at 16, 16 and 8; merges of 4, 8 and 16 copies at 16, 12 and 8.
+//  - the same with bounded counts, whose loads wait for more branches: 300 / B, 6 to 16,
+//    5 beyond B = 80 (g = 3, P = 5, B = 30: 157 us at 10, 164 at 8, 187 at 6; g = 8, P = 12,
+//    64: 297 at 6, 305 at 5 and 8; g = 8 with 12 fp32 copies, 88: 416 at 5, 427 at 6).
+//  - with unbounded counts, which have a batch of streams in flight: 10 where bf16
+//    copies are the most (g = 3, P = 40: 459 us, 510 at 7, 485 at 16), else 7 (g = 16, P = 8:
+//    400, 413 at 10, 438 at 16; g = 4 with 40 fp32 copies: 825, 853 and 905).
+//  - workgroups of four, with statistics: 4 up to B = 12 (92 us; 95 with 3), 3 up to
+//    36 (g = 4, P = 4: 177 us; 186 with 2, 180 with 4), else 2 (g = 8, P = 0: 204;
+//    219 with 3); unbounded counts as above 3 (478 us; 522 with 2, 501 with 4) or
+//    2 (425; 444 with 3).  g = 4, P = 32 and more are held at 2 or 1 by registers.
+//  - workgroups of four, without: 1 (g = 8, P = 32: 473 us against 499 with 2).
+//  - the pack (B = 4) needs the whole chip (24 us; 32 us with 16 wavefronts per CU).
+// A launch of up to 3M elements is not capped: it is over before the front has
+// spread, and a cap leaves it in more rounds than need be (g = 4, P = 8 without statistics,
+// capped and not: 0.5M elements 6.1 and 5.5 us, 1M 11.5 and 10.5, 2M 18.3 and 17.6, 4M
+// 34.3 and 34.0, 8M 63.9 and 66.4).
+// DASO_FUSED_WG_PER_CU replaces the count for the fused step (0: no cap).
+constexpr int64_t kUncapped = int64_t(3) << 20;
+int32_t lds_of(daso::Mode mode, bool with_stats, const daso::Shape& shape, const StepArgs& a, int64_t elems) {
+  if (mode == daso::kModePack) return 0;
   const int64_t over = fused_cap_override();
-  if (over >= 0) return daso::lds_for_workgroups_per_cu(static_cast<int32_t>(over));
-  return streams >= daso::kCapStreams ? daso::lds_for_workgroups_per_cu(daso::kCapWorkgroupsPerCU) : 0;
+  if (mode == daso::kModeFused && over >= 0) return daso::lds_for_workgroups_per_cu(static_cast<int32_t>(over));
+  int32_t bytes = a.P * (a.xf32 ? 4 : 2);
+  if (mode == daso::kModeAvg) bytes = 4 * a.g;
+  if (mode == daso::kModeMerge) bytes += 4;
+  if (mode == daso::kModeFused) bytes += 4 * a.g + 8;
+  if (elems <= kUncapped) return 0;
+  const bool unbounded = shape.counts == daso::Counts::kUnbounded;
+  const bool mostly_bf16 = !a.xf32 && a.P > a.g;
+  const auto share = [bytes](int32_t of, int32_t least) { return std::min(16, std::max(least, (of + bytes / 2) / bytes)); };
+  int32_t per_cu = 1;
+  if (shape.waves == 1) {
+    if (unbounded) per_cu = mostly_bf16 ? 10 : 7;
+    else if (shape.counts == daso::Counts::kBounded) per_cu = share(300, bytes > 80 ? 5 : 6);
+    else per_cu = share(mode == daso::kModeFused ? 190 : 240, 5);
+  } else if (with_stats) {
+    if (unbounded) per_cu = mostly_bf16 ? 3 : 2;
+    else per_cu = bytes <= 12 ? 4 : bytes <= 36 ? 3 : 2;
+  }
+  return daso::lds_for_workgroups_per_cu(per_cu);
 }
 
 // The current device, which must also be the device of `stream` (kernels run
@@ -207,169 +217,55 @@ int current_device(hipStream_t stream, int* dev) {
   return sdev == *dev ? DASO_OK : DASO_EINVAL;
 }
 
-// ----------------------------------------------------------- tile-order choice
-// The rule's run length is the best measured for most fused shapes, but some
-// (the segmentation-shaped step) run 2 to 5% faster in plain order.  For each
-// fused launch shape of a single launch, the first call is left out (it can
-// carry one-off costs: the first launch of a kernel in a process takes
-// milliseconds), then kTuneSamples calls alternate between the rule's run
-// length and plain order, each bracketed by two events on the call's stream.
-// Once all of them have completed, which later calls poll with hipEventQuery
-// (never waiting), plain order is kept for the shape if its fastest sample beat
-// the rule's by at least 1%, the rule's runs otherwise; until then calls take
-// the rule's run length.
-// The order never changes a result.  No sample is taken by a captured call, by
-// daso_fused_sync_step_noalloc (it only reads a choice already made), or when
-// DASO_FUSED_RUN_ELEMS or DASO_FUSED_TUNE=0 is set.
-constexpr int kTuneSkip = 1;                // calls of a shape before sampling starts
-constexpr int kTuneSamples = 6;             // rule, plain, rule, plain, rule, plain
-constexpr float kTunePlainMargin = 0.99f;   // plain order must be at least 1% faster
-
-bool tuning_enabled() {
-  static const bool v = env_count("DASO_FUSED_TUNE", 1, 1) != 0 && fused_run_elems_override() < 0;
-  return v;
-}
-
-struct TuneKey {
-  int dev;
-  int32_t g, P, xf32, stats, outputs;
-  int64_t n;
-  uint64_t layout;  // hash of the bucket table
-  bool operator<(const TuneKey& o) const {
-    if (dev != o.dev) return dev < o.dev;
-    if (g != o.g) return g < o.g;
-    if (P != o.P) return P < o.P;
-    if (xf32 != o.xf32) return xf32 < o.xf32;
-    if (stats != o.stats) return stats < o.stats;
-    if (outputs != o.outputs) return outputs < o.outputs;
-    if (n != o.n) return n < o.n;
-    return layout < o.layout;
-  }
-};
-
-struct Tune {
-  std::mutex mu;
-  hipEvent_t ev[kTuneSamples][2] = {};
-  int skipped = 0;     // calls left out before the first sample
-  int taken = 0;       // samples whose launches are queued
-  int32_t chosen = 0;  // tiles per run once decided, 0 before
-  bool off = false;    // an event call failed: keep the rule for this shape
-};
-
-std::mutex g_tune_mu;  // guards the map itself; nodes never move or go away
-std::map<TuneKey, Tune> g_tune;
-
-uint64_t layout_hash(const daso_bucket* b, int32_t nb) {
-  uint64_t h = 1469598103934665603ull;  // FNV-1a over the bucket ranges
-  auto mix = [&h](uint64_t v) {
-    for (int k = 0; k < 8; ++k) {
-      h ^= (v >> (8 * k)) & 0xFFu;
-      h *= 1099511628211ull;
-    }
-  };
-  for (int32_t i = 0; i < nb; ++i) {
-    mix(static_cast<uint64_t>(b[i].start));
-    mix(static_cast<uint64_t>(b[i].numel));
-  }
-  return h;
-}
-
-TuneKey tune_key(int dev, const StepArgs& a, bool with_stats, const daso_bucket* b, int32_t nb) {
-  int64_t n = 0;  // the buckets tile [0, n)
-  for (int32_t i = 0; i < nb; ++i) n += b[i].numel;
-  return TuneKey{dev, a.g, a.P, a.xf32, with_stats ? 1 : 0, (a.wire ? 1 : 0) | (a.gavg ? 2 : 0), n,
-                 layout_hash(b, nb)};
-}
-
-// The decided run length of a shape, or 0.  Never inserts.
-int32_t tuned_run(const TuneKey& k) {
-  std::lock_guard<std::mutex> lock(g_tune_mu);
-  const auto it = g_tune.find(k);
-  if (it == g_tune.end()) return 0;
-  std::lock_guard<std::mutex> tl(it->second.mu);
-  return it->second.chosen;
-}
-
-Tune& tune_entry(const TuneKey& k) {
-  std::lock_guard<std::mutex> lock(g_tune_mu);
-  return g_tune[k];
-}
-
-// With t.mu held, after all samples were queued: decide once every sample has
-// completed (calls of one shape may sample on different streams, so the last
-// queued need not be the last to finish).  The queries run only when no error
-// is pending on this thread, and any status they leave is cleared, so a
-// caller's error is neither consumed nor masked and none is left behind.
-void try_decide(Tune& t, int32_t rule) {
-  if (hipPeekAtLastError() != hipSuccess) return;
-  for (int k = 0; k < kTuneSamples; ++k) {
-    const hipError_t q = hipEventQuery(t.ev[k][1]);
-    if (q == hipSuccess) continue;
-    if (hipPeekAtLastError() != hipSuccess) (void)hipGetLastError();
-    if (q != hipErrorNotReady) t.off = true;
-    return;
-  }
-  float best[2] = {1e30f, 1e30f};
-  for (int k = 0; k < kTuneSamples; ++k) {
-    float ms = 0.0f;
-    if (hipEventElapsedTime(&ms, t.ev[k][0], t.ev[k][1]) != hipSuccess) {
-      if (hipPeekAtLastError() != hipSuccess) (void)hipGetLastError();
-      t.off = true;
-      return;
-    }
-    best[k % 2] = std::min(best[k % 2], ms);
-  }
-  // plain order only when it measured clearly faster: the rule's runs are the
-  // measured default, and two samples each cannot separate closer orders
-  t.chosen = best[1] < kTunePlainMargin * best[0] ? 1 : rule;
-  for (auto& e : t.ev) {
-    for (hipEvent_t& x : e) {
-      if (x) (void)hipEventDestroy(x);
-      x = nullptr;
-    }
-  }
-}
-
-// A failed HIP call made only for the sampling gives up sampling for the
-// shape; the error it left is dropped when no error was pending before it, so
-// that the library never leaves an error of its own behind.
-void give_up(Tune& t, bool was_clean) {
-  t.off = true;
-  if (was_clean && hipPeekAtLastError() != hipSuccess) (void)hipGetLastError();
-}
-
 // Where a fused launch with statistics keeps its tile partials and table.
 enum class Space {
   kAllocated,  // the per-(device, stream) workspace, allocated on first use
   kFixed,      // the fixed `scratch` array; calls needing more fail with DASO_ENOSPACE
 };
 
-int run_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb,
-               daso_bucket_stats* stats, hipStream_t stream, Space space = Space::kAllocated) {
+int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb,
+                  daso_bucket_stats* stats, hipStream_t stream, Space space) {
   const bool with_stats = (mode == daso::kModeFused) && stats != nullptr;
-  const int64_t tile = daso::tile_elems(mode, with_stats, a);
+  const int64_t tile = daso::plan_tile(mode, a.g, a.P, a.xf32 != 0);
   int64_t max_tiles = 1;
-  for (int32_t i = 0; i < nb; i += daso::kLaunchBuckets) {
-    const Group gr = group_at(b, nb, i, tile);
-    if (gr.ntiles > INT32_MAX) return DASO_EINVAL;
-    max_tiles = std::max(max_tiles, gr.ntiles);
+  for (int32_t i = 0; i < nb; i += daso::kPlanBuckets) {
+    const int64_t tiles = daso::plan_tiles(b, nb, i, tile);
+    if (tiles > INT32_MAX) return DASO_EINVAL;
+    max_tiles = std::max(max_tiles, tiles);
   }
-  // statistics scratch: the counter, the tile partials, then the table of bucket tile ranges
-  const size_t partials_at = daso::kStatsCounterBytes;
-  const size_t table_at = partials_at + static_cast<size_t>(max_tiles) * sizeof(TilePartial);
-  const size_t need = table_at + (daso::kLaunchBuckets + 1) * sizeof(int32_t);
-  if (with_stats && space == Space::kFixed && need > kScratchBytes) return DASO_ENOSPACE;
+  if (with_stats && space == Space::kFixed && daso::plan_scratch(max_tiles) > DASO_NOALLOC_SCRATCH_BYTES)
+    return DASO_ENOSPACE;
   int dev = 0;
   const int drc = current_device(stream, &dev);
   if (drc != DASO_OK) return drc;
-  const int streams = launch_streams(mode, a);
-  const int32_t lds = lds_of(mode, streams);
+  const Ranges ranges(b, nb, with_stats);
+  if (mode == daso::kModeMerge && a.P > 0 && a.wire == nullptr && ranges.size() == 1 && ranges[0].S == 0)
+    mode = daso::kModeMean;
+  a.g_inv = a.g > 0 ? 1.0f / static_cast<float>(a.g) : 0.0f;
+  const daso::Shape shape = daso::launch_shape(mode, with_stats, a);
+  const int shift = daso::super_shift(shape.waves);
+  const uint32_t lds = static_cast<uint32_t>(lds_of(mode, with_stats, shape, a, ranges[ranges.size() - 1].end));
+  // statistics scratch: the counter, the bucket table, the partials of every launch of the call
+  const size_t table_at = daso::kStatsCounterBytes;
+  const size_t partials_at = table_at + static_cast<size_t>(with_stats ? ranges.size() : 0) * sizeof(BucketSlots);
+  const int64_t room = space == Space::kFixed && with_stats
+                           ? (static_cast<int64_t>(kScratchBytes) - static_cast<int64_t>(partials_at)) /
+                                 static_cast<int64_t>(sizeof(SlicePartial))
+                           : INT64_MAX;
+  int64_t slots = 0, launches = 0;
+  for (int32_t i = 0; i < ranges.size(); ++launches) {
+    const Group g = daso::group_at(ranges, i, shift, room);
+    slots += daso::launch_slots(g, shift);
+    i += g.count;
+  }
+  // one statistics pass for the whole call when the partials of all its launches fit
+  // the scratch, else one after each launch
+  const bool pass_each = slots > room;
   std::unique_lock<std::mutex> hold;
   uint32_t* counter = nullptr;
-  bool capturing = true;  // unless the stream is known not to be capturing
   if (with_stats) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusActive;
-    capturing = hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
+    const bool capturing = hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
     void* base = nullptr;
     if (space == Space::kFixed) {
       ScratchSlot* slot = nullptr;
@@ -380,7 +276,7 @@ int run_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb,
     } else {
       Workspace& w = workspace_entry(dev, stream);
       hold = std::unique_lock<std::mutex>(w.mu);
-      const int rc = reserve(w, need);
+      const int rc = reserve(w, partials_at + static_cast<size_t>(slots) * sizeof(SlicePartial));
       if (rc != DASO_OK) return rc;
       base = w.ptr;
       // the last-workgroup statistics of small eager launches count in w's counter
@@ -390,80 +286,48 @@ int run_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb,
         counter = static_cast<uint32_t*>(base);
       }
     }
-    a.partials = reinterpret_cast<TilePartial*>(static_cast<char*>(base) + partials_at);
-    a.tile_table = reinterpret_cast<int32_t*>(static_cast<char*>(base) + table_at);
+    a.partials = reinterpret_cast<SlicePartial*>(static_cast<char*>(base) + partials_at);
+    a.table = reinterpret_cast<BucketSlots*>(static_cast<char*>(base) + table_at);
+    a.stats = stats;
   }
-  // the tile order of a single fused launch may be chosen per shape (above)
-  const bool choosable = mode == daso::kModeFused && streams >= daso::kXcdRunFusedStreams &&
-                         nb <= daso::kLaunchBuckets && tuning_enabled();
-  for (int32_t i = 0; i < nb; i += daso::kLaunchBuckets) {
-    const Group gr = group_at(b, nb, i, tile);
-    fill_group(a, b, gr, tile);
-    a.stats = with_stats ? stats + gr.first : nullptr;
-    // an eager launch of few tiles sums its own statistics in its last
-    // workgroup: that saves a launch's host cost (about 2.6 us) for fences that
+  BucketSlots* const table = a.table;
+  for (int32_t i = 0; i < ranges.size();) {
+    const Group g = daso::group_at(ranges, i, shift, room);
+    fill_group(a, ranges, g, shift);
+    // an eager launch of few workgroups sums its own statistics in its last
+    // one: that saves a launch's host cost (about 2.6 us) for fences that
     // cost the GPU about 0.1 us per workgroup; a graph replays launches without
     // that host cost, so a captured call keeps the statistics kernel (counter
     // stays null), and so does the no-alloc entry point, whose scratch every
     // call on the GPU shares: two of its calls racing on another stream could
     // leave a counter wrong for later calls, not only their own statistics
-    a.done = (counter != nullptr && a.ntiles <= daso::kFinishStatsMaxTiles) ? counter : nullptr;
-    const int32_t rule = xcd_run_of(mode, streams, a.ntiles, tile);
-    a.xcd_run = rule;
-    Tune* t = nullptr;
-    std::unique_lock<std::mutex> tl;
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    bool clean = true;  // no HIP error was pending when sampling started
-    if (choosable) {
-      const TuneKey key = tune_key(dev, a, with_stats, b, nb);
-      if (space == Space::kFixed) {
-        const int32_t c = tuned_run(key);
-        if (c > 0) a.xcd_run = c;
-      } else {
-        t = &tune_entry(key);
-        tl = std::unique_lock<std::mutex>(t->mu);
-        if (t->chosen > 0) {
-          a.xcd_run = t->chosen;
-        } else if (!t->off && t->skipped < kTuneSkip) {
-          ++t->skipped;
-        } else if (!t->off && t->taken < kTuneSamples) {
-          clean = hipPeekAtLastError() == hipSuccess;
-          hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-          if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
-            give_up(*t, clean);
-          } else if (cs == hipStreamCaptureStatusNone) {
-            hipEvent_t(&ev)[2] = t->ev[t->taken];
-            if ((ev[0] || hipEventCreate(&ev[0]) == hipSuccess) && (ev[1] || hipEventCreate(&ev[1]) == hipSuccess)) {
-              e0 = ev[0];
-              e1 = ev[1];
-              a.xcd_run = (t->taken % 2 == 0) ? rule : 1;
-            } else {
-              give_up(*t, clean);
-            }
-          }
-        } else if (!t->off && t->taken == kTuneSamples) {
-          try_decide(*t, rule);
-          if (t->chosen > 0) a.xcd_run = t->chosen;
-        }
-      }
+    a.done = launches == 1 && a.nslices <= daso::kFinishStatsMaxSlices ? counter : nullptr;
+    const int64_t row = daso::host::launch_grid(a.nslices, 1);
+    const dim3 grid(static_cast<uint32_t>(row), static_cast<uint32_t>((std::max<int64_t>(a.nslices, 1) + row - 1) / row));
+    if (daso::launch_step(mode, with_stats, a, grid, lds, stream) != hipSuccess) return DASO_EHIP;
+    i += g.count;
+    if (!with_stats || a.done != nullptr) continue;
+    if (pass_each || i == ranges.size()) {
+      const int32_t buckets = pass_each ? g.count : ranges.size();
+      if (daso::launch_stats(a.partials, table, stats, buckets, stream) != hipSuccess) return DASO_EHIP;
     }
-    const int64_t grid = daso::host::launch_grid(a.ntiles, a.xcd_run);
-    if (e0 && hipEventRecord(e0, stream) != hipSuccess) {
-      give_up(*t, clean);
-      e1 = nullptr;
-    }
-    if (daso::launch_step(mode, with_stats, a, static_cast<uint32_t>(grid), static_cast<uint32_t>(lds), stream) !=
-        hipSuccess)
-      return DASO_EHIP;
-    if (e1) {
-      if (hipEventRecord(e1, stream) == hipSuccess) {
-        ++t->taken;
-      } else {
-        give_up(*t, clean);
-      }
+    if (!pass_each) {
+      a.table += g.count;
+      a.slot0 += daso::launch_slots(g, shift);
     }
   }
   return DASO_OK;
+}
+
+// A long bucket table is sorted in host memory: running out of it must not
+// leave the C entry points as an exception.
+int run_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb,
+               daso_bucket_stats* stats, hipStream_t stream, Space space = Space::kAllocated) {
+  try {
+    return launch_groups(mode, a, b, nb, stats, stream, space);
+  } catch (const std::bad_alloc&) {
+    return DASO_EHIP;
+  }
 }
 
 }  // namespace
@@ -583,24 +447,17 @@ int daso_fused_launch_config(const daso_sync_args* args, daso_launch_config* out
   StepArgs a;
   const int rc = fused_args(args, a);
   if (rc != DASO_OK) return rc;
-  const bool with_stats = args->stats != nullptr;
-  const int64_t tile = daso::tile_elems(daso::kModeFused, with_stats, a);
-  const int streams = launch_streams(daso::kModeFused, a);
-  int64_t ntiles = 0;
-  if (args->n > 0)
-    for (int32_t k = 0; k < std::min<int32_t>(args->nbuckets, daso::kLaunchBuckets); ++k)
-      ntiles += daso::tiles_of(args->buckets[k].start, args->buckets[k].start + args->buckets[k].numel, tile);
+  const int64_t tile = daso::plan_tile(daso::kModeFused, a.g, a.P, a.xf32 != 0);
+  const int64_t ntiles = args->n > 0 ? daso::plan_tiles(args->buckets, args->nbuckets, 0, tile) : 0;
+  const int streams = a.g + a.P + 4 + (a.wire ? 1 : 0) + (a.gavg ? 1 : 0);
+  const int64_t run = fused_run_elems_override(), cap = fused_cap_override();
   out->tile_elems = tile;
   out->ntiles = ntiles;
-  out->xcd_run_tiles = xcd_run_of(daso::kModeFused, streams, std::max<int64_t>(ntiles, 1), tile);
-  out->lds_bytes = lds_of(daso::kModeFused, streams);
-  // a tile order already chosen for this shape on the current device replaces the rule's
-  int dev = 0;
-  if (args->n > 0 && streams >= daso::kXcdRunFusedStreams && args->nbuckets <= daso::kLaunchBuckets &&
-      tuning_enabled() && hipGetDevice(&dev) == hipSuccess) {
-    const int32_t c = tuned_run(tune_key(dev, a, with_stats, args->buckets, args->nbuckets));
-    if (c > 0) out->xcd_run_tiles = c;
-  }
+  out->xcd_run_tiles = daso::plan_run(streams, std::max<int64_t>(ntiles, 1));
+  if (run >= 0 && streams >= daso::kPlanRunStreams)
+    out->xcd_run_tiles = static_cast<int32_t>(std::max<int64_t>(1, run / tile));
+  out->lds_bytes = daso::lds_for_workgroups_per_cu(streams >= daso::kPlanCapStreams ? 2 : 0);
+  if (cap >= 0) out->lds_bytes = daso::lds_for_workgroups_per_cu(static_cast<int32_t>(cap));
   return DASO_OK;
 }
 

@@ -22,6 +22,22 @@
 
 #include "daso_launch.h"
 
+namespace daso {
+
+// Workgroups are dispatched to the 8 XCDs of the chip in turn (workgroup w to
+// XCD w % 8).  xcd_runs renumbers workgroup w so that each XCD takes runs of
+// `run` consecutive tiles: the k-th workgroup of XCD x in block b (of 8 * run
+// tiles) gets tile b * 8 * run + x * run + k.  Workgroups past the last whole
+// block keep their number.  A bijection of [0, grid); run = 1 is the identity.
+__device__ __forceinline__ int xcd_runs(int w, int grid, int run) {
+  const int block = 8 * run;
+  if (w >= (grid / block) * block) return w;
+  const int j = w >> 3, x = w & 7;
+  return (j / run) * block + x * run + (j % run);
+}
+
+}  // namespace daso
+
 namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));

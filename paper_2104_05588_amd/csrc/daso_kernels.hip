@@ -20,64 +20,37 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------ memory helpers
-// FULL: the 4-element vector lies inside the tile; otherwise `mask` selects
-// the elements to touch (bit k = element e0 + k) and the rest read as 0.
-template <bool FULL, bool STREAM>
-__device__ __forceinline__ f32x4 load_f32(const float* __restrict__ p, int64_t e0, unsigned mask) {
-  if constexpr (FULL) {
-    const f32x4* v = reinterpret_cast<const f32x4*>(p + e0);
-    if constexpr (STREAM) return __builtin_nontemporal_load(v);
-    else return *v;
-  } else {
-    f32x4 r = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (mask & (1u << k)) r[k] = p[e0 + k];
-    return r;
-  }
+// A wavefront's piece of a stream: `p` is the stream's base, `base` the piece's first
+// element (the same in every lane) and `off` the lane's first element within it.
+// The empty asm keeps the sum of the uniform part in scalar registers, so that
+// the access takes it with one 32-bit lane offset that all streams of a type share;
+// folded together they would cost each stream a 64-bit address and two
+// additions in the vector unit.
+#define DASO_GLOBAL __attribute__((address_space(1)))
+
+template <typename V, typename T>
+__device__ __forceinline__ V load_vec(const T* __restrict__ p, int64_t base, uint32_t off) {
+  auto q = (const DASO_GLOBAL char*)(p + base);
+  asm("" : "+s"(q));
+  return __builtin_nontemporal_load((const DASO_GLOBAL V*)(q + off * static_cast<uint32_t>(sizeof(T))));
 }
 
-template <bool FULL>
-__device__ __forceinline__ u32x2 load_bf16(const uint16_t* __restrict__ p, int64_t e0, unsigned mask) {
-  if constexpr (FULL) {
-    return __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p + e0));
-  } else {
-    uint32_t h[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (mask & (1u << k)) h[k] = p[e0 + k];
-    u32x2 r;
-    r.x = h[0] | (h[1] << 16);
-    r.y = h[2] | (h[3] << 16);
-    return r;
-  }
+template <typename V, typename T>
+__device__ __forceinline__ void store_vec(T* __restrict__ p, int64_t base, uint32_t off, V v) {
+  auto q = (DASO_GLOBAL char*)(p + base);
+  asm("" : "+s"(q));
+  __builtin_nontemporal_store(v, (DASO_GLOBAL V*)(q + off * static_cast<uint32_t>(sizeof(T))));
 }
 
-template <bool FULL, bool STREAM>
-__device__ __forceinline__ void store_f32(float* __restrict__ p, int64_t e0, unsigned mask, f32x4 v) {
-  if constexpr (FULL) {
-    f32x4* d = reinterpret_cast<f32x4*>(p + e0);
-    if constexpr (STREAM) __builtin_nontemporal_store(v, d);
-    else *d = v;
-  } else {
+// The elements of a vector that `mask` selects (bit k: element k); the others
+// read as 0.
+template <typename T>
+__device__ __forceinline__ void load_some(const T* __restrict__ p, unsigned mask, T (&r)[kVec]) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (mask & (1u << k)) p[e0 + k] = v[k];
-  }
-}
-
-template <bool FULL>
-__device__ __forceinline__ void store_bf16(uint16_t* __restrict__ p, int64_t e0, unsigned mask, u32x2 w) {
-  if constexpr (FULL) {
-    __builtin_nontemporal_store(w, reinterpret_cast<u32x2*>(p + e0));
-  } else {
-    const uint32_t h[4] = {w.x & 0xFFFFu, w.x >> 16, w.y & 0xFFFFu, w.y >> 16};
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (mask & (1u << k)) p[e0 + k] = static_cast<uint16_t>(h[k]);
-  }
+  for (int k = 0; k < kVec; ++k) r[k] = (mask & (1u << k)) ? p[k] : T(0);
 }
 
 // ------------------------------------------------------------ bf16 helpers
@@ -97,8 +70,21 @@ __device__ __forceinline__ u32x2 pack4(f32x4 v) {
   return w;
 }
 
+// The same for values of which none is NaN: the conversion instruction rounds
+// to nearest even and keeps subnormals; only its NaN patterns are other ones.
+__device__ __forceinline__ u32x2 pack4_no_nan(f32x4 v) {
+  return __builtin_bit_cast(u32x2, __builtin_convertvector(v, bf16x4));
+}
+
+// Whether any lane of the wavefront holds an infinity or a NaN in `v`.
+__device__ __forceinline__ bool any_nonfinite(f32x4 v) {
+  // x * 0 is 0 for every finite x and NaN otherwise
+  const float t = __builtin_fmaf(v.x, 0.0f, __builtin_fmaf(v.y, 0.0f, __builtin_fmaf(v.z, 0.0f, v.w * 0.0f)));
+  return __builtin_amdgcn_ballot_w64(t != t) != 0;
+}
+
 // Exact bfloat16 -> binary32: the pattern becomes the top half.
-__device__ __forceinline__ f32x4 widen4(u32x2 h) {
+__device__ __forceinline__ f32x4 widen(u32x2 h) {
   f32x4 r;
   r.x = __uint_as_float(h.x << 16);
   r.y = __uint_as_float(h.x & 0xFFFF0000u);
@@ -111,60 +97,61 @@ __device__ __forceinline__ f32x4 widen4(u32x2 h) {
 // the non-blocking exchange of Section 3, which is not cast).
 template <bool XF>
 struct XType {
-  using T = u32x2;
+  using Elem = uint16_t;
+  using Vec = u32x2;
+  static __device__ __forceinline__ f32x4 received(Vec v) { return widen(v); }
+  static __device__ __forceinline__ Vec sent(f32x4 v) { return pack4(v); }
+  static __device__ __forceinline__ Vec sent_finite(f32x4 v) { return pack4_no_nan(v); }
+  static __device__ __forceinline__ Vec joined(const Elem (&h)[kVec]) {
+    return Vec{h[0] | (static_cast<uint32_t>(h[1]) << 16), h[2] | (static_cast<uint32_t>(h[3]) << 16)};
+  }
 };
 template <>
 struct XType<true> {
-  using T = f32x4;
+  using Elem = float;
+  using Vec = f32x4;
+  static __device__ __forceinline__ f32x4 received(Vec v) { return v; }
+  static __device__ __forceinline__ Vec sent(f32x4 v) { return v; }
+  static __device__ __forceinline__ Vec sent_finite(f32x4 v) { return v; }
+  static __device__ __forceinline__ Vec joined(const Elem (&h)[kVec]) { return Vec{h[0], h[1], h[2], h[3]}; }
 };
 
-template <bool XF, bool FULL>
-__device__ __forceinline__ typename XType<XF>::T load_x(const void* p, int64_t e0, unsigned mask) {
-  if constexpr (XF) return load_f32<FULL, true>(static_cast<const float*>(p), e0, mask);
-  else return load_bf16<FULL>(static_cast<const uint16_t*>(p), e0, mask);
-}
-
-template <bool XF>
-__device__ __forceinline__ f32x4 received(typename XType<XF>::T v) {
-  if constexpr (XF) return v;
-  else return widen4(v);
-}
-
-template <bool XF, bool FULL>
-__device__ __forceinline__ void store_wire(void* p, int64_t e0, unsigned mask, f32x4 v) {
-  if constexpr (XF) store_f32<FULL, true>(static_cast<float*>(p), e0, mask, v);
-  else store_bf16<FULL>(static_cast<uint16_t*>(p), e0, mask, pack4(v));
-}
-
-// Division by a per-bucket or per-call constant.  For a power of two the
-// product with its (exact) reciprocal equals the correctly rounded quotient.
+// Division by a per-bucket or per-call integer d, correctly rounded.  For a power
+// of two it is the product with the (exact) reciprocal.  Else q = RN(a * y) with
+// y = RN(1 / d) is corrected once by its exact remainder (Markstein 1990): q' =
+// RN(q + y * (a - d * q)) is the correctly rounded quotient as long as the
+// remainder is representable, which tiny a can violate: they (below 2^-100)
+// take the plain division.  Zeros, infinities and NaN are set right by
+// v_div_fixup.
 struct Divisor {
   float d;
   float inv;
   bool pow2;
 };
 
-__device__ __forceinline__ Divisor make_divisor(int k) {
-  Divisor v;
-  v.d = static_cast<float>(k);
-  v.pow2 = k > 0 && (k & (k - 1)) == 0;
-  v.inv = v.pow2 ? 1.0f / v.d : 0.0f;
-  return v;
+__device__ __forceinline__ Divisor make_divisor(int k, float inv) {
+  return Divisor{static_cast<float>(k), inv, k > 0 && (k & (k - 1)) == 0};
+}
+
+__device__ __forceinline__ float quotient(float a, const Divisor& q) {
+  const float z = a * q.inv;
+  return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-z, q.d, a), q.inv, z), q.d, a);
 }
 
 __device__ __forceinline__ f32x4 divide(f32x4 a, const Divisor& q) {
   if (q.pow2) return a * q.inv;
-  f32x4 r;
-  r.x = a.x / q.d;
-  r.y = a.y / q.d;
-  r.z = a.z / q.d;
-  r.w = a.w / q.d;
-  return r;
+  // twice the pattern of |a|, less one: zero becomes the largest value
+  const auto key = [](float v) { return 2u * __float_as_uint(v) - 1u; };
+  const uint32_t least = min(min(key(a.x), key(a.y)), min(key(a.z), key(a.w)));
+  constexpr uint32_t kTiny = 2u * ((127u - 100u) << 23) - 1u;  // 2^-100
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(least < kTiny) == 0, 1))
+    return f32x4{quotient(a.x, q), quotient(a.y, q), quotient(a.z, q), quotient(a.w, q)};
+  return f32x4{a.x / q.d, a.y / q.d, a.z / q.d, a.w / q.d};
 }
 
 // --------------------------------------------------------------- statistics
-// Per-thread sums over a tile (the count fits 32 bits: at most 32 elements per
-// thread); the cross-tile reduction uses a 64-bit count.
+// Sums of a thread (the count fits 32 bits: at most 4 elements per thread and
+// partial) or across slices (64-bit count).
 template <typename CountT>
 struct AccT {
   double gsq;
@@ -174,60 +161,103 @@ struct AccT {
 using Acc = AccT<uint32_t>;
 using Acc64 = AccT<uint64_t>;
 
-__device__ __forceinline__ void accumulate(Acc& acc, f32x4 gbar, f32x4 xl, f32x4 xn, unsigned mask) {
+// The squares of binary32 values are exact in binary64, so the fused
+// multiply-add rounds as a multiplication and an addition would.
+__device__ __forceinline__ void accumulate(Acc& acc, f32x4 gbar, f32x4 xl, f32x4 xn, unsigned mask, bool nonfinite) {
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
+  for (int k = 0; k < kVec; ++k) {
     if (mask & (1u << k)) {
       const double gv = static_cast<double>(gbar[k]);
       const double dv = static_cast<double>(xn[k]) - static_cast<double>(xl[k]);
-      acc.gsq += gv * gv;
-      acc.dsq += dv * dv;
-      acc.nf += ((__float_as_uint(xn[k]) & 0x7F800000u) == 0x7F800000u) ? 1u : 0u;
+      acc.gsq = __builtin_fma(gv, gv, acc.gsq);
+      acc.dsq = __builtin_fma(dv, dv, acc.dsq);
     }
+  }
+  if (nonfinite) {
+#pragma unroll
+    for (int k = 0; k < kVec; ++k)
+      if ((mask & (1u << k)) && (__float_as_uint(xn[k]) & 0x7F800000u) == 0x7F800000u) ++acc.nf;
   }
 }
 
-// Deterministic block sum: a fixed xor-butterfly inside each wavefront, then the
-// wavefront sums in index order.  Result valid in thread 0.
-template <typename CountT>
-__device__ __forceinline__ AccT<CountT> block_sum(AccT<CountT> v) {
-  __shared__ double s_g[kBlock / 64];
-  __shared__ double s_d[kBlock / 64];
-  __shared__ CountT s_n[kBlock / 64];
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    v.gsq += __shfl_xor(v.gsq, off, 64);
-    v.dsq += __shfl_xor(v.dsq, off, 64);
-    v.nf += __shfl_xor(v.nf, off, 64);
+// One step of a wavefront sum: the value plus that of the lane which the DPP
+// control names (0 where it names none).
+template <int CTRL, typename T>
+__device__ __forceinline__ T dpp_add(T v) {
+  if constexpr (sizeof(T) == 4) {
+    return v + __builtin_bit_cast(
+                   T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+  } else {
+    const u32x2 u = __builtin_bit_cast(u32x2, v);
+    u32x2 r;
+    r.x = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(u.x), CTRL, 0xF, 0xF, true));
+    r.y = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(u.y), CTRL, 0xF, 0xF, true));
+    return v + __builtin_bit_cast(T, r);
   }
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
-    s_g[wave] = v.gsq;
-    s_d[wave] = v.dsq;
-    s_n[wave] = v.nf;
-  }
+}
+
+// Sum over the wavefront in a fixed tree: within rows of 16 lanes, then across
+// the rows.  Valid in lane 63.  DPP moves stay in the vector ALU; a shuffle goes
+// through LDS and takes several times as long, while the workgroup holds its place
+// on the CU with no loads in flight.
+template <typename T>
+__device__ __forceinline__ T wave_sum(T v) {
+  v = dpp_add<0x111>(v);  // row_shr:1
+  v = dpp_add<0x112>(v);  // row_shr:2
+  v = dpp_add<0x114>(v);  // row_shr:4
+  v = dpp_add<0x118>(v);  // row_shr:8
+  v = dpp_add<0x142>(v);  // row_bcast:15
+  v = dpp_add<0x143>(v);  // row_bcast:31
+  return v;
+}
+
+// Two sums at once: the halves of the wavefront first trade, so that the lower half
+// holds a's partial sums and the upper one b's; one tree then serves both.
+// The sum of `a` is valid in lane 31, that of `b` in lane 63.
+__device__ __forceinline__ double wave_sum2(double a, double b) {
+  const u32x2 ua = __builtin_bit_cast(u32x2, a), ub = __builtin_bit_cast(u32x2, b);
+  const auto lo = __builtin_amdgcn_permlane32_swap(ua.x, ub.x, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(ua.y, ub.y, false, false);
+  double v = __builtin_bit_cast(double, u32x2{lo[0], hi[0]}) + __builtin_bit_cast(double, u32x2{lo[1], hi[1]});
+  v = dpp_add<0x111>(v);
+  v = dpp_add<0x112>(v);
+  v = dpp_add<0x114>(v);
+  v = dpp_add<0x118>(v);
+  return dpp_add<0x142>(v);  // row_bcast:15: lane 31 and lane 63 hold their half's sum
+}
+
+// The sums of a workgroup's wavefronts, in LDS.
+template <int kWaves>
+struct WaveSums {
+  double sq[kWaves][2];  // grad_sq, delta_sq
+  uint64_t nf[kWaves];
+};
+
+// Deterministic block sum: each wavefront's sum, then those in index order.
+// Valid in thread 0.  The caller puts a barrier between two uses of `s`.
+template <typename CountT, int kWaves>
+__device__ __forceinline__ Acc64 block_sum(const AccT<CountT>& v, WaveSums<kWaves>& s) {
+  const double t = wave_sum2(v.gsq, v.dsq);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  CountT n = 0;
+  if (__builtin_amdgcn_ballot_w64(v.nf != 0) != 0) n = wave_sum(v.nf);
+  if ((lane & 31) == 31) s.sq[wave][lane >> 5] = t;
+  if (lane == 63) s.nf[wave] = n;
   __syncthreads();
-  AccT<CountT> r = {0.0, 0.0, 0};
+  Acc64 r = {0.0, 0.0, 0};
   if (threadIdx.x == 0) {
-    for (int w = 0; w < kBlock / 64; ++w) {
-      r.gsq += s_g[w];
-      r.dsq += s_d[w];
-      r.nf += s_n[w];
+    r = Acc64{s.sq[0][0], s.sq[0][1], s.nf[0]};
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) {
+      r.gsq += s.sq[w][0];
+      r.dsq += s.sq[w][1];
+      r.nf += s.nf[w];
     }
   }
-  __syncthreads();
   return r;
 }
 
-// ------------------------------------------- arithmetic shared by both paths
-// The local average's output: the local-average entry point stores it
-// (streaming); the fused step stores it only when asked for.
-template <int MODE, bool FULL>
-__device__ __forceinline__ void store_avg(const StepArgs& a, int64_t e0, unsigned mask, f32x4 gbar) {
-  if constexpr (MODE == kModeAvg) store_f32<FULL, true>(a.gavg, e0, mask, gbar);
-  else if (a.gavg) store_f32<FULL, false>(a.gavg, e0, mask, gbar);
-}
-
+// ---------------------------------------------------- arithmetic of a vector
 // The start of Eq. (1)'s sum: the local term 2S * xl.  S = 0 is the blocking
 // synchronisation of Section 3, the plain average of the exchanged copies, so
 // the local state is left out: the sum starts from -0, the identity of IEEE
@@ -247,104 +277,143 @@ __device__ __forceinline__ f32x4 sgd_momentum4(const StepArgs& a, f32x4 x, f32x4
   return x - (a.lr * m);
 }
 
+// A result of a wavefront's piece: whole, or (FULL = false) the elements of each
+// lane's vector that its `mask` selects.
+template <bool FULL, typename V, typename T>
+__device__ __forceinline__ void put(T* __restrict__ p, int64_t base, uint32_t off, unsigned mask, V v) {
+  if constexpr (FULL) {
+    store_vec(p, base, off, v);
+  } else {
+    if (mask == 0xFu) {
+      __builtin_nontemporal_store(v, reinterpret_cast<V*>(p + base + off));
+    } else {
+      T h[kVec];
+      __builtin_memcpy(h, &v, sizeof(v));
+#pragma unroll
+      for (int k = 0; k < kVec; ++k)
+        if (mask & (1u << k)) p[base + off + k] = h[k];
+    }
+  }
+}
+
 // The outputs after the merge: params, the wire (of x' or, with
 // DASO_PACK_PRE_MERGE, of xl) and the statistics.
-template <int MODE, bool FULL, bool STATS, bool XF>
-__device__ __forceinline__ void store_results(const StepArgs& a, int64_t e0, unsigned mask, f32x4 gbar, f32x4 xl,
-                                              f32x4 xn, Acc& acc) {
-  store_f32<FULL, kNtParams>(a.x, e0, mask, xn);
+template <int MODE, bool STATS, bool XF, bool FULL>
+__device__ __forceinline__ void store_results(const StepArgs& a, int64_t base, uint32_t off, unsigned mask,
+                                              f32x4 gbar, f32x4 xl, f32x4 xn, Acc& acc) {
+  using X = XType<XF>;
+  put<FULL>(a.x, base, off, mask, xn);
+  bool nonfinite = false;
+  if constexpr (STATS || !XF) nonfinite = any_nonfinite(xn);
   if (a.wire) {
+    auto* wire = static_cast<typename X::Elem*>(a.wire);
     const bool pre = (MODE == kModeFused) && (a.flags & DASO_PACK_PRE_MERGE);
-    store_wire<XF, FULL>(a.wire, e0, mask, pre ? xl : xn);
+    const f32x4 y = pre ? xl : xn;
+    if (__builtin_expect(!nonfinite && !pre, 1)) put<FULL>(wire, base, off, mask, X::sent_finite(y));
+    else put<FULL>(wire, base, off, mask, X::sent(y));
   }
-  if constexpr (STATS && MODE == kModeFused) accumulate(acc, gbar, xl, xn, mask);
+  if constexpr (STATS && MODE == kModeFused) accumulate(acc, gbar, xl, xn, mask, nonfinite);
 }
 
-// ----------------------------------------------------------- one 4-vector
-// Stream counts known only at run time: each input is folded in as it loads.
-template <int MODE, int G, int PP, bool FULL, bool STATS, bool XF>
-__device__ __forceinline__ void step_vec(const StepArgs& a, int64_t e0, unsigned mask, float two_s,
-                                         const Divisor& qg, const Divisor& qm, Acc& acc) {
-  if constexpr (MODE == kModePack) {
-    const f32x4 v = load_f32<FULL, true>(a.src, e0, mask);
-    store_wire<false, FULL>(a.wire, e0, mask, v);
-    return;
-  }
-  const int g = (G > 0) ? G : a.g;
-  const int P = (PP >= 0) ? PP : a.P;
-
-  f32x4 gbar = {0.f, 0.f, 0.f, 0.f};
-  if constexpr (MODE == kModeAvg || MODE == kModeFused) {
-    f32x4 s = load_f32<FULL, true>(a.grads[0], e0, mask);
-#pragma unroll
-    for (int r = 1; r < g; ++r) s = s + load_f32<FULL, true>(a.grads[r], e0, mask);
-    gbar = divide(s, qg);
-    store_avg<MODE, FULL>(a, e0, mask, gbar);
-    if constexpr (MODE == kModeAvg) return;
-  }
-
-  const f32x4 x = load_f32<FULL, kNtParams>(a.x, e0, mask);
-  f32x4 xl = x;
-  if constexpr (MODE == kModeFused) {
-    f32x4 m = load_f32<FULL, kNtParams>(a.m, e0, mask);
-    xl = sgd_momentum4(a, x, m, gbar);
-    store_f32<FULL, kNtParams>(a.m, e0, mask, m);
-  }
-
-  f32x4 xn = xl;
-  if (P > 0) {
-    f32x4 acc4 = merge_start(two_s, xl);
-#pragma unroll
-    for (int i = 0; i < P; ++i) acc4 = acc4 + received<XF>(load_x<XF, FULL>(a.stale[i], e0, mask));
-    xn = divide(acc4, qm);
-  }
-  store_results<MODE, FULL, STATS, XF>(a, e0, mask, gbar, xl, xn, acc);
-}
-
-// ------------------------------------- batched vectors (stream counts known)
-// All loads of a batch of vectors are issued before the first store, so that a
-// wavefront keeps every stream of several vectors in flight at once (the
-// compiler cannot move later loads above earlier stores by itself: it cannot
-// prove that the streams do not overlap).
+// ------------------------------------------------- a vector of every stream
+// All loads of a piece are issued before its first store, so that a wavefront
+// keeps every stream in flight at once (the compiler cannot move later loads
+// above earlier stores by itself: it cannot prove that the streams do not
+// overlap).
 // Stream counts: G > 0 and PP >= 0 are exact; G < 0 and PP <= -2 are run-time
-// counts bounded by -G and -PP, whose missing streams are skipped (predicated);
-// G == 0 and PP == -1 are unbounded run-time counts (the step_vec path).
+// counts bounded by -G and -PP, whose missing streams are skipped; G == 0 and
+// PP == -1 are unbounded run-time counts (step_any).
 template <int G>
 constexpr int g_slots() { return G > 0 ? G : (G < 0 ? -G : 0); }
 template <int PP>
 constexpr int p_slots() { return PP >= 0 ? PP : (PP <= -2 ? -PP : 0); }
 
+constexpr bool has_grads(int mode) { return mode == kModeAvg || mode == kModeFused; }
+constexpr bool has_copies(int mode) { return mode == kModeMerge || mode == kModeMean || mode == kModeFused; }
+constexpr bool reads_x(int mode) { return mode == kModeMerge || mode == kModeFused; }
+
 template <int MODE, int G, int PP, bool XF>
 struct VecIn {
-  static constexpr int kG = (MODE == kModeAvg || MODE == kModeFused) ? g_slots<G>() : 0;
-  static constexpr int kP = (MODE == kModeMerge || MODE == kModeFused) ? p_slots<PP>() : 0;
+  static constexpr int kG = has_grads(MODE) ? g_slots<G>() : 0;
+  static constexpr int kP = has_copies(MODE) ? p_slots<PP>() : 0;
   f32x4 g[kG > 0 ? kG : 1];
   f32x4 x;  // params (merge, fused) or the source (pack)
   f32x4 m;  // momentum (fused)
-  typename XType<XF>::T s[kP > 0 ? kP : 1];
+  typename XType<XF>::Vec s[kP > 0 ? kP : 1];
 };
 
-template <int MODE, int G, int PP, bool XF, bool FULL>
-__device__ __forceinline__ void load_in(const StepArgs& a, int64_t e0, unsigned mask, VecIn<MODE, G, PP, XF>& v) {
-  using V = VecIn<MODE, G, PP, XF>;
-#pragma unroll
-  for (int r = 0; r < V::kG; ++r)
-    if (G > 0 || r < a.g) v.g[r] = load_f32<FULL, true>(a.grads[r], e0, mask);
-  if constexpr (MODE == kModePack) v.x = load_f32<FULL, true>(a.src, e0, mask);
-  if constexpr (MODE == kModeMerge || MODE == kModeFused) v.x = load_f32<FULL, kNtParams>(a.x, e0, mask);
-  if constexpr (MODE == kModeFused) v.m = load_f32<FULL, kNtParams>(a.m, e0, mask);
-#pragma unroll
-  for (int i = 0; i < V::kP; ++i)
-    if (PP >= 0 || i < a.P) v.s[i] = load_x<XF, FULL>(a.stale[i], e0, mask);
+// A stream pointer that is to be in scalar registers from here on: with run-time
+// counts each load sits behind a branch of its own, and reading its pointer there too
+// would make every load wait for the one before.
+template <bool HOLD, typename T>
+__device__ __forceinline__ T* held(T* p) {
+  if constexpr (HOLD) asm("" : "+s"(p));
+  return p;
 }
 
-template <int MODE, int G, int PP, bool XF, bool FULL, bool STATS>
-__device__ __forceinline__ void finish(const StepArgs& a, int64_t e0, unsigned mask,
+// Every stream's vector at base + off.
+template <int MODE, int G, int PP, bool XF>
+__device__ __forceinline__ void load_in(const StepArgs& a, int64_t base, uint32_t off, VecIn<MODE, G, PP, XF>& v) {
+  using V = VecIn<MODE, G, PP, XF>;
+  using X = XType<XF>;
+  if constexpr (MODE == kModePack) v.x = load_vec<f32x4>(a.src, base, off);
+  if constexpr (V::kG > 0) {
+    const float* p[V::kG];
+#pragma unroll
+    for (int r = 0; r < V::kG; ++r) p[r] = held<(G < 0)>(a.grads[r]);
+#pragma unroll
+    for (int r = 0; r < V::kG; ++r)
+      if (G > 0 || r < a.g) v.g[r] = load_vec<f32x4>(p[r], base, off);
+  }
+  if constexpr (reads_x(MODE)) v.x = load_vec<f32x4>(a.x, base, off);
+  if constexpr (MODE == kModeFused) v.m = load_vec<f32x4>(a.m, base, off);
+  constexpr int kHold = 8;
+#pragma unroll
+  for (int i = 0; i < V::kP; i += kHold) {
+    const void* p[kHold];
+#pragma unroll
+    for (int j = 0; j < kHold; ++j)
+      if (i + j < V::kP) p[j] = held<(PP < 0)>(a.stale[i + j]);
+#pragma unroll
+    for (int j = 0; j < kHold; ++j)
+      if (i + j < V::kP && (PP >= 0 || i + j < a.P))
+        v.s[i + j] = load_vec<typename X::Vec>(static_cast<const typename X::Elem*>(p[j]), base, off);
+  }
+}
+
+// The elements of every stream's vector at element e0 that `mask` selects.
+template <int MODE, int G, int PP, bool XF>
+__device__ __forceinline__ void load_some_in(const StepArgs& a, int64_t e0, unsigned mask, VecIn<MODE, G, PP, XF>& v) {
+  using V = VecIn<MODE, G, PP, XF>;
+  using X = XType<XF>;
+  const auto f32 = [&](const float* p) {
+    float h[kVec];
+    load_some(p + e0, mask, h);
+    return f32x4{h[0], h[1], h[2], h[3]};
+  };
+#pragma unroll
+  for (int r = 0; r < V::kG; ++r)
+    if (G > 0 || r < a.g) v.g[r] = f32(a.grads[r]);
+  if constexpr (MODE == kModePack) v.x = f32(a.src);
+  if constexpr (reads_x(MODE)) v.x = f32(a.x);
+  if constexpr (MODE == kModeFused) v.m = f32(a.m);
+#pragma unroll
+  for (int i = 0; i < V::kP; ++i)
+    if (PP >= 0 || i < a.P) {
+      typename X::Elem h[kVec];
+      load_some(static_cast<const typename X::Elem*>(a.stale[i]) + e0, mask, h);
+      v.s[i] = X::joined(h);
+    }
+}
+
+template <int MODE, int G, int PP, bool XF, bool STATS, bool FULL>
+__device__ __forceinline__ void finish(const StepArgs& a, int64_t base, uint32_t off, unsigned mask,
                                        const VecIn<MODE, G, PP, XF>& v, float two_s, const Divisor& qg,
                                        const Divisor& qm, Acc& acc) {
   using V = VecIn<MODE, G, PP, XF>;
+  using X = XType<XF>;
   if constexpr (MODE == kModePack) {
-    store_wire<false, FULL>(a.wire, e0, mask, v.x);
+    put<FULL>(static_cast<uint16_t*>(a.wire), base, off, mask, any_nonfinite(v.x) ? pack4(v.x) : pack4_no_nan(v.x));
     return;
   }
   f32x4 gbar = {0.f, 0.f, 0.f, 0.f};
@@ -354,123 +423,156 @@ __device__ __forceinline__ void finish(const StepArgs& a, int64_t e0, unsigned m
     for (int r = 1; r < V::kG; ++r)
       if (G > 0 || r < a.g) s = s + v.g[r];
     gbar = divide(s, qg);
-    store_avg<MODE, FULL>(a, e0, mask, gbar);
+    if (MODE == kModeAvg || a.gavg) put<FULL>(a.gavg, base, off, mask, gbar);
     if constexpr (MODE == kModeAvg) return;
   }
-  f32x4 xl = v.x;
+  f32x4 xl = {0.f, 0.f, 0.f, 0.f};  // (mean) not used: 2S is 0
+  if constexpr (reads_x(MODE)) xl = v.x;
   if constexpr (MODE == kModeFused) {
     f32x4 m = v.m;
     xl = sgd_momentum4(a, v.x, m, gbar);
-    store_f32<FULL, kNtParams>(a.m, e0, mask, m);
+    put<FULL>(a.m, base, off, mask, m);
   }
   f32x4 xn = xl;
   if constexpr (V::kP > 0) {
     if (PP >= 0 || a.P > 0) {
-      f32x4 acc4 = merge_start(two_s, xl);
+      f32x4 sum = merge_start(two_s, xl);
 #pragma unroll
       for (int i = 0; i < V::kP; ++i)
-        if (PP >= 0 || i < a.P) acc4 = acc4 + received<XF>(v.s[i]);
-      xn = divide(acc4, qm);
+        if (PP >= 0 || i < a.P) sum = sum + X::received(v.s[i]);
+      xn = divide(sum, qm);
     }
   }
-  store_results<MODE, FULL, STATS, XF>(a, e0, mask, gbar, xl, xn, acc);
+  store_results<MODE, STATS, XF, FULL>(a, base, off, mask, gbar, xl, xn, acc);
 }
 
-// Whether an instance has compile-time stream counts or bounds (and so the
-// batched path).
+// Whether an instance has compile-time stream counts or bounds, and so takes
+// every stream's vector before the first addition.
 template <int MODE, int G, int PP>
 constexpr bool batched() {
   if constexpr (MODE == kModePack) return true;
   if constexpr (MODE == kModeAvg) return G != 0;
-  if constexpr (MODE == kModeMerge) return PP != -1;
+  if constexpr (MODE == kModeMerge || MODE == kModeMean) return PP != -1;
   return G != 0 && PP != -1;
 }
 
-// Vectors per thread and tile: a batch of kBatch when a vector's inputs fit in
-// 48 VGPRs, else one (measured: 2048-element tiles are best for the 40-register
-// resnet50 step, 1024-element tiles for the 56- and 104-register ones); the
-// runtime-count instances take kGenericIters vectors one after the other.
-template <int MODE, int G, int PP, bool XF>
-constexpr int iters_of() {
-  if constexpr (!batched<MODE, G, PP>()) {
-    return kGenericIters;
-  } else {
-    using V = VecIn<MODE, G, PP, XF>;
-    constexpr int regs = 4 * V::kG + (XF ? 4 : 2) * V::kP + ((MODE == kModeFused) ? 8 : 4);
-    return regs <= 48 ? kBatch : 1;
-  }
+template <int MODE, int G, int PP>
+constexpr Counts counts_of() {
+  if (!batched<MODE, G, PP>()) return Counts::kUnbounded;
+  return (has_grads(MODE) && G < 0) || (has_copies(MODE) && PP < 0) ? Counts::kBounded : Counts::kExact;
 }
 
-template <int MODE, int G, int PP, bool XF>
-constexpr int64_t tile_of() {
-  return int64_t(kBlock) * kVec * iters_of<MODE, G, PP, XF>();
-}
-
-// ------------------------------------------------------------------- tiles
+// Wavefronts per workgroup.  With statistics 4, which share one partial (one
+// wavefront each took the resnet50-shaped step from 206.7 to 207.4 us and the
+// GPT-shaped one from 6960 to 7120: four times the partials to write and to sum).
+// Without them one, so that a place on a CU is free again as soon as its own loads and
+// stores are done (resnet50-shaped 196 against 204 us, the average of 8 gradients
+// 140 against 145, g = 8 with 12 fp32 copies 406 against 437), except for exact
+// counts that take 88 bytes per element or more: there 4 wavefronts on one CU run 1 to 6%
+// faster than 4 spread over the chip (g = 8, P = 32: 473 against 486 us).
 template <int MODE, int G, int PP, bool STATS, bool XF>
-__device__ __forceinline__ void run_tile(const StepArgs& a, int64_t abase, int64_t tlo, int64_t thi, float two_s,
-                                         const Divisor& qg, const Divisor& qm, Acc& acc) {
-  constexpr bool kBatched = batched<MODE, G, PP>();
-  constexpr int kIters = iters_of<MODE, G, PP, XF>();
-  const int64_t t0 = abase + int64_t(threadIdx.x) * kVec;
-  if constexpr (kBatched) {
-    if (tlo == abase && thi == abase + tile_of<MODE, G, PP, XF>()) {
-      // a whole tile: all loads of the thread's kIters vectors, then the stores
-      VecIn<MODE, G, PP, XF> v[kIters];
-#pragma unroll
-      for (int b = 0; b < kIters; ++b) load_in<MODE, G, PP, XF, true>(a, t0 + int64_t(b) * kBlock * kVec, 0xFu, v[b]);
-#pragma unroll
-      for (int b = 0; b < kIters; ++b)
-        finish<MODE, G, PP, XF, true, STATS>(a, t0 + int64_t(b) * kBlock * kVec, 0xFu, v[b], two_s, qg, qm, acc);
-      return;
-    }
-  }
-  for (int it = 0; it < kIters; ++it) {
-    const int64_t e0 = t0 + int64_t(it) * kBlock * kVec;
-    const bool full = e0 >= tlo && e0 + kVec <= thi;
-    unsigned mask = 0xFu;
-    if (!full) {
-      if (e0 + kVec <= tlo || e0 >= thi) continue;
-      mask = 0;
-#pragma unroll
-      for (int k = 0; k < kVec; ++k)
-        if (e0 + k >= tlo && e0 + k < thi) mask |= 1u << k;
-    }
-    if constexpr (kBatched) {
-      if (full) {
-        VecIn<MODE, G, PP, XF> v;
-        load_in<MODE, G, PP, XF, true>(a, e0, mask, v);
-        finish<MODE, G, PP, XF, true, STATS>(a, e0, mask, v, two_s, qg, qm, acc);
-      } else {
-        // A vector cut by the bucket edge takes its elements one by one; folding
-        // each stream in as it loads keeps this rarely run path from holding
-        // every stream's addresses and values at once, which would otherwise set
-        // the register count, and so the occupancy, of the whole kernel.
-        step_vec<MODE, G, PP, false, STATS, XF>(a, e0, mask, two_s, qg, qm, acc);
-      }
-    } else {
-      if (full) step_vec<MODE, G, PP, true, STATS, XF>(a, e0, mask, two_s, qg, qm, acc);
-      else step_vec<MODE, G, PP, false, STATS, XF>(a, e0, mask, two_s, qg, qm, acc);
-    }
+constexpr int waves_of() {
+  using V = VecIn<MODE, G, PP, XF>;
+  constexpr int bytes = 4 * V::kG + (XF ? 4 : 2) * V::kP + (MODE == kModeFused ? 8 : reads_x(MODE) ? 4 : 0);
+  return STATS || (counts_of<MODE, G, PP>() == Counts::kExact && bytes >= 88) ? 4 : 1;
+}
+
+// ------------------------------------------------- unbounded run-time counts
+template <bool FULL, typename V, typename T>
+__device__ __forceinline__ V get(const T* p, int64_t base, uint32_t off, unsigned mask) {
+  if constexpr (FULL) {
+    return load_vec<V>(p, base, off);
+  } else {
+    T h[kVec];
+    load_some(p + base + off, mask, h);
+    V v;
+    __builtin_memcpy(&v, h, sizeof(v));
+    return v;
   }
 }
 
-// The statistics of one bucket: the whole workgroup sums the tile partials
-// [t0, t1) in a fixed assignment and reduction tree (thread k adds partials
-// t0 + k, t0 + k + kBlock, ... in that order), so the result does not depend on
-// timing, on which kernel runs it or on kLoads.  Valid in thread 0.
+// sum + p[0] + p[1] + ...  Streams come in batches, the loads of a batch all
+// issued before its additions, which run in stream order.  Batches of 8 leave room
+// for enough wavefronts to cover their latency (g = 4, P = 64 and g = 3, P = 40, 25.6M
+// parameters: 690 and 459 us; batches of 16 712 and 472, with the next batch loaded before
+// this one's additions 714 and 473).
+template <bool XF, bool FULL>
+__device__ __forceinline__ f32x4 add_streams(f32x4 sum, const void* const* p, int count, int64_t base, uint32_t off,
+                                             unsigned mask) {
+  using X = XType<XF>;
+  constexpr int kBatch = 8;
+  static_assert(DASO_MAX_G % kBatch == 0 && DASO_MAX_P % kBatch == 0, "a batch's pointers lie within StepArgs' arrays");
+  for (int i = 0; i < count; i += kBatch) {
+    const void* q[kBatch];
+    typename X::Vec t[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) q[j] = held<FULL>(p[i + j]);
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j)
+      if (i + j < count) t[j] = get<FULL, typename X::Vec>(static_cast<const typename X::Elem*>(q[j]), base, off, mask);
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j)
+      if (i + j < count) sum = sum + X::received(t[j]);
+  }
+  return sum;
+}
+
+template <int MODE, bool STATS, bool XF, bool FULL>
+__device__ __forceinline__ void step_any(const StepArgs& a, int64_t base, uint32_t off, unsigned mask, float two_s,
+                                         const Divisor& qg, const Divisor& qm, Acc& acc) {
+  f32x4 xl = {0.f, 0.f, 0.f, 0.f};  // (mean) not used: 2S is 0
+  f32x4 m = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (reads_x(MODE)) xl = get<FULL, f32x4>(a.x, base, off, mask);
+  if constexpr (MODE == kModeFused) m = get<FULL, f32x4>(a.m, base, off, mask);
+  f32x4 gbar = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (has_grads(MODE)) {
+    // -0 + G_0 == G_0 for every G_0
+    gbar = divide(add_streams<true, FULL>(f32x4{-0.0f, -0.0f, -0.0f, -0.0f},
+                                          reinterpret_cast<const void* const*>(a.grads), a.g, base, off, mask), qg);
+    if (MODE == kModeAvg || a.gavg) put<FULL>(a.gavg, base, off, mask, gbar);
+    if constexpr (MODE == kModeAvg) return;
+  }
+  if constexpr (MODE == kModeFused) {
+    xl = sgd_momentum4(a, xl, m, gbar);
+    put<FULL>(a.m, base, off, mask, m);
+  }
+  f32x4 xn = xl;
+  if (a.P > 0) xn = divide(add_streams<XF, FULL>(merge_start(two_s, xl), a.stale, a.P, base, off, mask), qm);
+  store_results<MODE, STATS, XF, FULL>(a, base, off, mask, gbar, xl, xn, acc);
+}
+
+// ------------------------------------------------------------------ buckets
+// The bucket of the launch that holds element e: the last whose start is not
+// past it (buckets are sorted by start; of several at one start all but the last
+// are empty).
+__device__ __forceinline__ int bucket_of(const StepArgs& a, int64_t e) {
+  int lo = 0, hi = a.nb - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (a.start[mid] <= e) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
+// The statistics of one bucket: the whole workgroup sums the partials [t0, t1)
+// in a fixed assignment and reduction tree (thread k adds partials t0 + k,
+// t0 + k + kBlock, ... in that order), so the result does not depend on timing,
+// on which kernel runs it or on kLoads.  Valid in thread 0.
 // The sum is latency-bound: each thread issues the loads of up to kLoads
-// partials before it adds them in tile order.  Missing ones count as zeros,
-// which leaves every sum unchanged (sums of squares are never -0).
-template <int kLoads>
-__device__ __forceinline__ Acc64 bucket_stats(const TilePartial* partials, int t0, int t1) {
+// partials before it adds them in order.  Missing ones count as zeros, which
+// leaves every sum unchanged (sums of squares are never -0).
+template <int kLoads, int kWaves>
+__device__ __forceinline__ Acc64 bucket_stats(const SlicePartial* partials, int64_t t0, int64_t t1,
+                                              WaveSums<kWaves>& s) {
+  constexpr int kThreads = 64 * kWaves;
   Acc64 v = {0.0, 0.0, 0};
-  for (int base = t0 + static_cast<int>(threadIdx.x); base < t1; base += kBlock * kLoads) {
-    TilePartial p[kLoads];
+  for (int64_t base = t0 + static_cast<int64_t>(threadIdx.x); base < t1; base += kThreads * kLoads) {
+    SlicePartial p[kLoads];
 #pragma unroll
     for (int u = 0; u < kLoads; ++u) {
-      const int j = base + u * kBlock;
-      p[u] = j < t1 ? partials[j] : TilePartial{0.0, 0.0, 0};
+      const int64_t j = base + u * kThreads;
+      p[u] = j < t1 ? partials[j] : SlicePartial{0.0, 0.0, 0};
     }
 #pragma unroll
     for (int u = 0; u < kLoads; ++u) {
@@ -479,7 +581,8 @@ __device__ __forceinline__ Acc64 bucket_stats(const TilePartial* partials, int t
       v.nf += p[u].nonfinite;
     }
   }
-  return block_sum(v);
+  __syncthreads();  // s may still be read from the call before
+  return block_sum(v, s);
 }
 
 __device__ __forceinline__ void put_stats(daso_bucket_stats* out, const Acc64& r) {
@@ -488,77 +591,133 @@ __device__ __forceinline__ void put_stats(daso_bucket_stats* out, const Acc64& r
   out->nonfinite = r.nf;
 }
 
-// A launch of few tiles sums its statistics in its own last workgroup instead
+// The partials of bucket i of a launch.
+template <int SHIFT>
+__device__ __forceinline__ BucketSlots slots_of(const StepArgs& a, int i) {
+  const int64_t bs = a.start[i], be = a.start[i + 1];
+  const int64_t first = a.slot0 + slot_of((bs >> SHIFT) - a.sb0, i);
+  return BucketSlots{first, be > bs ? a.slot0 + slot_of(((be - 1) >> SHIFT) - a.sb0, i) + 8 : first, a.out[i]};
+}
+
+// A launch of few workgroups sums its statistics in its own last workgroup instead
 // of a second launch.  Each workgroup makes its partials visible to the whole
 // chip (an agent-scope release fence: the XCD's L2 writes them back) and then
 // counts itself done; the one that counts last takes an acquire fence and sums
-// every bucket with the same code and order as stats_kernel, so the results
-// are the same bits, and sets the counter back to zero for the next launch.
-// The fences cost about 0.1 us per workgroup, which is why only small launches
-// (at most kFinishStatsMaxTiles tiles, one workgroup each) take this path.
-__device__ __forceinline__ void finish_stats_if_last(const StepArgs& a) {
+// every bucket in the order of stats_kernel (no thread has more than one partial to
+// add, so that the smaller workgroup changes nothing), and sets the
+// counter back to zero for the next launch.
+template <int SHIFT, int kWaves>
+__device__ __forceinline__ void finish_stats_if_last(const StepArgs& a, WaveSums<kWaves>& s) {
   __shared__ bool last;
   __syncthreads();  // thread 0 has written this workgroup's partials
   if (threadIdx.x == 0) {
     __threadfence();
-    last = atomicAdd(a.done, 1u) == gridDim.x - 1;
+    last = atomicAdd(a.done, 1u) == gridDim.x - 1;  // such a launch has one row of workgroups
   }
   __syncthreads();
   if (!last) return;
   __threadfence();
   for (int i = 0; i < a.nb; ++i) {
-    const int t1 = i + 1 < a.nb ? a.b[i + 1].first_tile : a.ntiles;
-    const Acc64 r = bucket_stats<1>(a.partials, a.b[i].first_tile, t1);  // at most one partial per thread
-    if (threadIdx.x == 0) put_stats(a.stats + i, r);
+    const BucketSlots t = slots_of<SHIFT>(a, i);
+    const Acc64 r = bucket_stats<1>(a.partials, t.first, t.end, s);
+    if (threadIdx.x == 0) put_stats(a.stats + t.out, r);
   }
   if (threadIdx.x == 0) atomicExch(a.done, 0u);
 }
 
 // ------------------------------------------------------------------- kernel
-// One workgroup per tile; the loop serves a grid smaller than the tiles (the
-// host caps the grid for launches of more than 2^20 tiles).
-template <int MODE, int G, int PP, bool STATS, bool XF>
-__global__ __launch_bounds__(kBlock) void step_kernel(const StepArgs a) {
-  constexpr int64_t kTile = tile_of<MODE, G, PP, XF>();
-  const int P = (PP >= 0) ? PP : a.P;
-  const Divisor qg = make_divisor((G > 0) ? G : a.g);
-  const int w0 = a.xcd_run > 1 ? xcd_runs(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x), a.xcd_run)
-                               : static_cast<int>(blockIdx.x);
-  if constexpr (STATS && MODE == kModeFused) {
-    // the bucket ranges for stats_kernel (the grid has at least one workgroup)
-    const int k = static_cast<int>(threadIdx.x);
-    if (blockIdx.x == 0 && k <= a.nb) a.tile_table[k] = k < a.nb ? a.b[k].first_tile : a.ntiles;
-  }
-  for (int64_t t = w0; t < a.ntiles; t += gridDim.x) {
-    const int tile = static_cast<int>(t);
-    // bucket owning this tile: the last one whose first tile is <= tile
-    int lo = 0, hi = a.nb - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (a.b[mid].first_tile <= tile) lo = mid;
-      else hi = mid - 1;
-    }
-    const TileBucket bk = a.b[lo];
-    const int64_t abase = (bk.start / kTile + int64_t(tile - bk.first_tile)) * kTile;  // on the tile grid
-    const int64_t tlo = bk.start > abase ? bk.start : abase;
-    const int64_t thi = bk.end < abase + kTile ? bk.end : abase + kTile;
-    const float two_s = static_cast<float>(2 * bk.S);
-    const Divisor qm = make_divisor(2 * bk.S + P);
+// The elements of the vector at e0 that lie in [lo, hi), as a mask.
+__device__ __forceinline__ unsigned vec_mask(int64_t e0, int64_t lo, int64_t hi) {
+  unsigned mask = 0;
+#pragma unroll
+  for (int k = 0; k < kVec; ++k)
+    if (e0 + k >= lo && e0 + k < hi) mask |= 1u << k;
+  return mask;
+}
 
-    Acc acc = {0.0, 0.0, 0u};
-    run_tile<MODE, G, PP, STATS, XF>(a, abase, tlo, thi, two_s, qg, qm, acc);
-    if constexpr (STATS && MODE == kModeFused) {
-      const Acc t = block_sum(acc);
-      if (threadIdx.x == 0) {
-        TilePartial* pt = a.partials + tile;
-        pt->grad_sq = t.gsq;
-        pt->delta_sq = t.dsq;
-        pt->nonfinite = static_cast<uint64_t>(t.nf);
+// One workgroup per slice (see the work decomposition in daso_launch.h).
+//
+// The step is bound by HBM: while a wavefront's loads are not in flight, its place
+// on the CU is idle, so everything else is kept off the way to them.  The loads depend
+// on nothing but the workgroup's index; the bucket (the staleness S, the
+// place of its statistics) is looked up while they are in flight.  Against the
+// tiles that came before (2048 or 1024 elements of one bucket each, in runs per XCD,
+// looked up first), same buffers in turn: ragged step 82.7 to 78.0 us, many small
+// buckets 712 to 680, resnet50-shaped 216 to 206 (without statistics 213.5 to 196),
+// the average of 8 gradients 444 to 399, merges 5 to 9% faster; boxes differ by a few percent.
+template <int MODE, int G, int PP, bool STATS, bool XF>
+__global__ __launch_bounds__((64 * waves_of<MODE, G, PP, STATS, XF>())) void step_kernel(const StepArgs a) {
+  constexpr bool kBatched = batched<MODE, G, PP>();
+  constexpr bool kStats = STATS && MODE == kModeFused;
+  constexpr int kWaves = waves_of<MODE, G, PP, STATS, XF>();
+  constexpr int kShift = super_shift(kWaves);
+  const int64_t w = (int64_t(blockIdx.y) << kRowShift) + blockIdx.x;
+  const int wave = kWaves == 1 ? 0 : __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const uint32_t off = (threadIdx.x & 63u) * kVec;  // of the lane's elements in its piece
+  const int64_t sbase = (a.sb0 + (w >> 3)) << kShift;
+  const int64_t base = sbase + (wave * 8 + static_cast<int>(w & 7)) * kPiece;
+  const bool whole = base >= a.lo && base + kPiece <= a.hi;
+  // the buckets that overlap the superblock (with statistics: the workgroup
+  // writes a partial for each) or the piece
+  const int64_t from = kStats ? sbase : base, to = kStats ? sbase + (int64_t(1) << kShift) : base + kPiece;
+  const Divisor qg = (G > 0) ? make_divisor(G, 1.0f / (G > 0 ? G : 1)) : make_divisor(a.g, a.g_inv);
+  const int P = (PP >= 0) ? PP : a.P;
+  __shared__ WaveSums<kWaves> s_sum;
+  const auto put_partial = [&](int b, const Acc& acc) {
+    const Acc64 t = block_sum(acc, s_sum);
+    if (threadIdx.x == 0) {
+      const int64_t slot = a.slot0 + slot_of((sbase >> kShift) - a.sb0, b) + (w & 7);
+      a.partials[slot] = SlicePartial{t.gsq, t.dsq, t.nf};
+    }
+  };
+  VecIn<MODE, G, PP, XF> v;
+  int b = 0;
+  bool done = false;
+  if (__builtin_expect(whole, 1)) {
+    if constexpr (kBatched) load_in<MODE, G, PP, XF>(a, base, off, v);
+    b = bucket_of(a, from > a.lo ? from : a.lo);
+    if (__builtin_expect(from >= a.start[b] && to <= a.start[b + 1], 1)) {  // all in one bucket
+      const Divisor qm = make_divisor(2 * a.S[b] + P, a.inv[b]);
+      const float two_s = static_cast<float>(2 * a.S[b]);
+      Acc acc = {0.0, 0.0, 0u};
+      if constexpr (kBatched) finish<MODE, G, PP, XF, STATS, true>(a, base, off, 0xFu, v, two_s, qg, qm, acc);
+      else step_any<MODE, STATS, XF, true>(a, base, off, 0xFu, two_s, qg, qm, acc);
+      if constexpr (kStats) put_partial(b, acc);
+      done = true;
+    }
+  } else {
+    done = w >= a.nslices;
+    if (!done) {
+      b = bucket_of(a, from > a.lo ? from : a.lo);
+      if constexpr (kBatched) {
+        const unsigned mask = vec_mask(base + off, a.lo, a.hi);
+        if (mask) load_some_in<MODE, G, PP, XF>(a, base + off, mask, v);
       }
     }
   }
-  if constexpr (STATS && MODE == kModeFused) {
-    if (a.done != nullptr) finish_stats_if_last(a);
+  if (!done) {
+    // one bucket after the other; each lane stores the elements of its vector that lie in it
+    for (;; ++b) {
+      const Divisor qm = make_divisor(2 * a.S[b] + P, a.inv[b]);
+      const float two_s = static_cast<float>(2 * a.S[b]);
+      Acc acc = {0.0, 0.0, 0u};
+      const unsigned mask = vec_mask(base + off, a.start[b], a.start[b + 1]);
+      if (mask) {
+        if constexpr (kBatched) finish<MODE, G, PP, XF, STATS, false>(a, base, off, mask, v, two_s, qg, qm, acc);
+        else step_any<MODE, STATS, XF, false>(a, base, off, mask, two_s, qg, qm, acc);
+      }
+      if constexpr (kStats) {
+        put_partial(b, acc);
+        __syncthreads();  // before s_sum is written again
+      }
+      if (b + 1 >= a.nb || a.start[b + 1] >= to) break;
+    }
+  }
+  if constexpr (kStats) {
+    static_assert(64 * kWaves >= kLaunchBuckets, "one thread per bucket writes the table");
+    // for stats_kernel (the grid has at least one workgroup)
+    if (w == 0 && threadIdx.x < a.nb) a.table[threadIdx.x] = slots_of<kShift>(a, static_cast<int>(threadIdx.x));
+    if (a.done != nullptr) finish_stats_if_last<kShift>(a, s_sum);
   }
 }
 
@@ -568,84 +727,81 @@ __global__ void clear_counter_kernel(uint32_t* counter) {
   if (threadIdx.x == 0) *counter = 0u;
 }
 
-// Statistics of one launch: workgroup i sums the tile partials of bucket i.
+// Statistics of one launch: workgroup i sums the partials of bucket i.
 // Runs after step_kernel on the same stream, which makes every partial, and the
-// tile table, visible without any fence inside step_kernel.
-__global__ __launch_bounds__(kBlock) void stats_kernel(const StatsArgs a) {
-  const int i = static_cast<int>(blockIdx.x);
-  // 16 loads per thread in flight: about 12 partials each for a 25 MiB bucket of 2048-element tiles
-  const Acc64 r = bucket_stats<16>(a.partials, a.tile_table[i], a.tile_table[i + 1]);
-  if (threadIdx.x == 0) put_stats(a.stats + i, r);
+// table, visible without any fence inside step_kernel.
+__global__ __launch_bounds__(kStatsBlock) void stats_kernel(const StatsArgs a) {
+  __shared__ WaveSums<kStatsBlock / 64> s_sum;
+  const BucketSlots t = a.table[blockIdx.x];
+  // 8 loads per thread in flight: a 25 MiB bucket has about 6 partials for each
+  const Acc64 r = bucket_stats<8>(a.partials, t.first, t.end, s_sum);
+  if (threadIdx.x == 0) put_stats(a.stats + t.out, r);
 }
 
-// Fused instances with compile-time stream counts for the node shapes: g = 4
-// or 8 replicas (the GPUs of a node) with P in {2, 4, 8, 16, 32} exchanged
-// copies (the nodes of a group), bf16 or fp32, and the local step (P = 0).
-// Other pairs run an instance with bounded counts (below) or the run-time-count
-// instance, which measured 3 to 7% slower than exact ones on the node shapes.
-template <bool STATS, typename F>
+// Fused instances: compile-time stream counts for the node shapes, g = 4 or 8
+// replicas (the GPUs of a node) with P in {2, 4, 8, 16, 32, 64} exchanged copies (the
+// nodes of a group), and for the local step (P = 0); counts bounded by 4 or 8
+// replicas and 8, 16 or 32 copies for the rest, whose missing streams are
+// skipped; unbounded run-time counts beyond 8 replicas or 32 copies.  A bound of 64
+// copies does not fit the registers of two wavefronts per SIMD (g = 3, P = 40: 574
+// us against 497 with unbounded counts); for a few streams less than its bound an instance
+// loses nothing (g = 5, P = 20 with a bound of 32: 332 us against 456 unbounded).
+template <bool STATS, bool XF, int GB, typename F>
+auto dispatch_bounded(const StepArgs& a, const F& f) {
+  if (a.P <= 8) return f.template run<kModeFused, GB, -8, STATS, XF>();
+  if (a.P <= 16) return f.template run<kModeFused, GB, -16, STATS, XF>();
+  if (a.P <= 32) return f.template run<kModeFused, GB, -32, STATS, XF>();
+  return f.template run<kModeFused, 0, -1, STATS, XF>();
+}
+
+template <bool STATS, bool XF, int G, typename F>
+auto dispatch_node(const StepArgs& a, const F& f) {
+  switch (a.P) {
+    case 0: return f.template run<kModeFused, G, 0, STATS, XF>();
+    case 2: return f.template run<kModeFused, G, 2, STATS, XF>();
+    case 4: return f.template run<kModeFused, G, 4, STATS, XF>();
+    case 8: return f.template run<kModeFused, G, 8, STATS, XF>();
+    case 16: return f.template run<kModeFused, G, 16, STATS, XF>();
+    case 32: return f.template run<kModeFused, G, 32, STATS, XF>();
+    default: break;
+  }
+  if constexpr (!XF)
+    if (a.P == 64) return f.template run<kModeFused, G, 64, STATS, false>();
+  return dispatch_bounded<STATS, XF, -G>(a, f);
+}
+
+template <bool STATS, bool XF, typename F>
 auto dispatch_fused(const StepArgs& a, const F& f) {
-  if (a.xf32) {
-    if (a.g == 4 || a.g == 8) {
-      const bool g8 = a.g == 8;
-      switch (a.P) {
-        case 2: return g8 ? f.template run<kModeFused, 8, 2, STATS, true>() : f.template run<kModeFused, 4, 2, STATS, true>();
-        case 4: return g8 ? f.template run<kModeFused, 8, 4, STATS, true>() : f.template run<kModeFused, 4, 4, STATS, true>();
-        case 8: return g8 ? f.template run<kModeFused, 8, 8, STATS, true>() : f.template run<kModeFused, 4, 8, STATS, true>();
-        case 16: return g8 ? f.template run<kModeFused, 8, 16, STATS, true>() : f.template run<kModeFused, 4, 16, STATS, true>();
-        case 32: return g8 ? f.template run<kModeFused, 8, 32, STATS, true>() : f.template run<kModeFused, 4, 32, STATS, true>();
-        default: break;
-      }
-    }
-    return f.template run<kModeFused, 0, -1, STATS, true>();
+  if (a.g > 8) return f.template run<kModeFused, 0, -1, STATS, XF>();
+  if (a.g == 4) return dispatch_node<STATS, XF, 4>(a, f);
+  if (a.g == 8) return dispatch_node<STATS, XF, 8>(a, f);
+  if (!XF && a.P == 0) {
+    if (a.g == 1) return f.template run<kModeFused, 1, 0, STATS, false>();
+    if (a.g == 2) return f.template run<kModeFused, 2, 0, STATS, false>();
   }
-  if (a.P == 0) {  // the local step of most cycling batches (no copies arrive)
-    switch (a.g) {
-      case 1: return f.template run<kModeFused, 1, 0, STATS, false>();
-      case 2: return f.template run<kModeFused, 2, 0, STATS, false>();
-      case 4: return f.template run<kModeFused, 4, 0, STATS, false>();
-      case 8: return f.template run<kModeFused, 8, 0, STATS, false>();
-      default: break;
-    }
+  if (a.g < 4) return dispatch_bounded<STATS, XF, -4>(a, f);
+  return dispatch_bounded<STATS, XF, -8>(a, f);
+}
+
+template <int MODE, bool XF, typename F>
+auto dispatch_merge(const StepArgs& a, const F& f) {
+  switch (a.P) {
+    case 0: return f.template run<kModeMerge, 0, 0, false, XF>();  // never the mean of nothing
+    case 2: return f.template run<MODE, 0, 2, false, XF>();
+    case 4: return f.template run<MODE, 0, 4, false, XF>();
+    case 8: return f.template run<MODE, 0, 8, false, XF>();
+    case 16: return f.template run<MODE, 0, 16, false, XF>();
+    case 32: return f.template run<MODE, 0, 32, false, XF>();
+    default: break;
   }
-  if (a.g == 4) {
-    switch (a.P) {
-      case 2: return f.template run<kModeFused, 4, 2, STATS, false>();
-      case 4: return f.template run<kModeFused, 4, 4, STATS, false>();
-      case 8: return f.template run<kModeFused, 4, 8, STATS, false>();
-      case 16: return f.template run<kModeFused, 4, 16, STATS, false>();
-      case 32: return f.template run<kModeFused, 4, 32, STATS, false>();
-      default: break;
-    }
-  }
-  if (a.g == 8) {
-    switch (a.P) {
-      case 2: return f.template run<kModeFused, 8, 2, STATS, false>();
-      case 4: return f.template run<kModeFused, 8, 4, STATS, false>();
-      case 8: return f.template run<kModeFused, 8, 8, STATS, false>();
-      case 16: return f.template run<kModeFused, 8, 16, STATS, false>();
-      case 32: return f.template run<kModeFused, 8, 32, STATS, false>();
-      default: break;
-    }
-  }
-  // other counts up to 8 replicas and 16 copies: instances bounded by 4 or 8
-  // and 8 or 16 streams, the missing ones skipped (measured 4 to 7% faster than
-  // the run-time-count instance there; slower beyond 16 copies, and no faster
-  // for g = 8 with fewer than 8 copies)
-  if (a.g <= 4 && a.P <= 16) {
-    if (a.P <= 8) return f.template run<kModeFused, -4, -8, STATS, false>();
-    return f.template run<kModeFused, -4, -16, STATS, false>();
-  }
-  if (a.g <= 8 && a.P <= 16 && (a.g < 8 || a.P > 8)) {
-    if (a.P <= 8) return f.template run<kModeFused, -8, -8, STATS, false>();
-    return f.template run<kModeFused, -8, -16, STATS, false>();
-  }
-  return f.template run<kModeFused, 0, -1, STATS, false>();
+  if (a.P <= 8) return f.template run<MODE, 0, -8, false, XF>();
+  if (a.P <= 16) return f.template run<MODE, 0, -16, false, XF>();
+  if (a.P <= 32) return f.template run<MODE, 0, -32, false, XF>();
+  return f.template run<MODE, 0, -1, false, XF>();
 }
 
 // The instance for a call, chosen in one place: `f.template run<MODE, G, PP,
-// STATS, XF>()` is called for it, both to launch and to size the tiles, so the
-// two always agree.  Fully unrolled instances exist for common stream counts;
+// STATS, XF>()` is called for it.  Fully unrolled instances exist for common stream counts;
 // any other count takes the runtime-count instance, which computes the same bits.
 template <typename F>
 auto dispatch(Mode mode, bool with_stats, const StepArgs& a, const F& f) {
@@ -662,27 +818,12 @@ auto dispatch(Mode mode, bool with_stats, const StepArgs& a, const F& f) {
       }
     case kModePack:
       return f.template run<kModePack, 0, -1, false, false>();
-    case kModeMerge:
-      if (a.xf32) {
-        if (a.P == 8) return f.template run<kModeMerge, 0, 8, false, true>();
-        return f.template run<kModeMerge, 0, -1, false, true>();
-      }
-      switch (a.P) {
-        case 0: return f.template run<kModeMerge, 0, 0, false, false>();
-        case 2: return f.template run<kModeMerge, 0, 2, false, false>();
-        case 4: return f.template run<kModeMerge, 0, 4, false, false>();
-        case 8: return f.template run<kModeMerge, 0, 8, false, false>();
-        case 16: return f.template run<kModeMerge, 0, 16, false, false>();
-        case 32: return f.template run<kModeMerge, 0, 32, false, false>();
-        default:
-          if (a.P <= 8) return f.template run<kModeMerge, 0, -8, false, false>();
-          if (a.P <= 16) return f.template run<kModeMerge, 0, -16, false, false>();
-          return f.template run<kModeMerge, 0, -1, false, false>();
-      }
+    case kModeMerge: return a.xf32 ? dispatch_merge<kModeMerge, true>(a, f) : dispatch_merge<kModeMerge, false>(a, f);
+    case kModeMean: return a.xf32 ? dispatch_merge<kModeMean, true>(a, f) : dispatch_merge<kModeMean, false>(a, f);
     case kModeFused:
     default:
-      if (with_stats) return dispatch_fused<true>(a, f);
-      return dispatch_fused<false>(a, f);
+      if (a.xf32) return with_stats ? dispatch_fused<true, true>(a, f) : dispatch_fused<false, true>(a, f);
+      return with_stats ? dispatch_fused<true, false>(a, f) : dispatch_fused<false, false>(a, f);
   }
 }
 
@@ -691,37 +832,38 @@ auto dispatch(Mode mode, bool with_stats, const StepArgs& a, const F& f) {
 // this call nor consumed by it.
 struct Launcher {
   const StepArgs& a;
-  uint32_t grid;
+  dim3 grid;
   uint32_t lds;  // LDS held per workgroup (unused by the kernel; caps workgroups per CU)
   hipStream_t stream;
   template <int MODE, int G, int PP, bool STATS, bool XF>
   hipError_t run() const {
     void* args[] = {const_cast<StepArgs*>(&a)};
-    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(&step_kernel<MODE, G, PP, STATS, XF>),
-                                         dim3(grid), dim3(kBlock), args, lds, stream);
-    if (e != hipSuccess || !STATS || a.done != nullptr) return e;
-    StatsArgs sa = {a.partials, a.tile_table, a.stats, a.nb};
-    void* sargs[] = {&sa};
-    return hipLaunchKernel(reinterpret_cast<const void*>(&stats_kernel), dim3(a.nb), dim3(kBlock), sargs, 0, stream);
+    return hipLaunchKernel(reinterpret_cast<const void*>(&step_kernel<MODE, G, PP, STATS, XF>), grid,
+                           dim3(64 * waves_of<MODE, G, PP, STATS, XF>()), args, lds, stream);
   }
 };
 
-struct TileSize {
+struct ShapeOf {
   template <int MODE, int G, int PP, bool STATS, bool XF>
-  int64_t run() const {
-    return tile_of<MODE, G, PP, XF>();
+  Shape run() const {
+    return Shape{waves_of<MODE, G, PP, STATS, XF>(), counts_of<MODE, G, PP>()};
   }
 };
 
 }  // namespace
 
-int64_t tile_elems(Mode mode, bool with_stats, const StepArgs& a) {
-  return dispatch(mode, with_stats, a, TileSize{});
+Shape launch_shape(Mode mode, bool with_stats, const StepArgs& a) { return dispatch(mode, with_stats, a, ShapeOf{}); }
+
+hipError_t launch_step(Mode mode, bool with_stats, const StepArgs& a, dim3 grid, uint32_t lds, hipStream_t stream) {
+  return dispatch(mode, with_stats, a, Launcher{a, grid, lds, stream});
 }
 
-hipError_t launch_step(Mode mode, bool with_stats, const StepArgs& a, uint32_t grid, uint32_t lds,
-                       hipStream_t stream) {
-  return dispatch(mode, with_stats, a, Launcher{a, grid, lds, stream});
+hipError_t launch_stats(const SlicePartial* partials, const BucketSlots* table, daso_bucket_stats* stats, int32_t nb,
+                        hipStream_t stream) {
+  StatsArgs a = {partials, table, stats};
+  void* args[] = {&a};
+  return hipLaunchKernel(reinterpret_cast<const void*>(&stats_kernel), dim3(static_cast<uint32_t>(nb)),
+                         dim3(kStatsBlock), args, 0, stream);
 }
 
 hipError_t clear_stats_counter(void* buffer, hipStream_t stream) {

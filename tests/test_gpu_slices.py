@@ -1,0 +1,130 @@
+"""The step's split into pieces of 256 elements at the sizes where it can go
+wrong: around a piece, a superblock of 2048 or 8192 elements and the 16-byte
+vector, with buckets that begin and end inside a piece, several in one piece and
+empty ones, for every kind of instance (exact, bounded and unbounded counts, with one and
+four wavefronts per workgroup, both exchange types); and tables of more buckets than one launch
+takes.  Against the oracle, bit for bit (statistics: fp64 sums in another order,
+1e-10)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2104_05588_amd as daso
+from oracle import daso_oracle as O
+from tests.test_gpu_parity import (F32, announce, check_f32, check_stats, check_u16, compare_fused, dev_bf16, dev_f32,
+                                   host_f32, host_u16, random_inputs, run_fused)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    daso.load()
+    yield
+    torch.cuda.synchronize()
+
+
+SIZES = [1, 255, 256, 257, 2047, 2048, 2051, 8190, 8192, 8197, 16_384, 24_579]
+
+
+def edge_buckets(rng, n):
+    """Buckets tiling [0, n) whose edges lie on, just before and just after the
+    split's own, with a few of one to three elements and an empty one, in random order."""
+    near = [e + d for e in range(0, n + 1, 256) for d in (-3, -1, 0, 1) if 0 < e + d < n]
+    cuts = sorted(set(rng.choice(near, min(len(near), 12), replace=False).tolist())) if near else []
+    if cuts:
+        cuts = sorted(set(cuts + [c + 1 for c in cuts[:2] if c + 1 < n] + [c + 3 for c in cuts[:2] if c + 3 < n]))
+    edges = [0] + cuts + [n]
+    bks = [(a, b - a, int(rng.choice((0, 1, 2, 3, 8)))) for a, b in zip(edges[:-1], edges[1:])]
+    bks.append((edges[len(edges) // 2], 0, 5))
+    return [bks[i] for i in rng.permutation(len(bks))]
+
+
+@pytest.mark.parametrize("stats", [False, True])
+@pytest.mark.parametrize("g,P,f32", [(4, 8, False), (8, 32, False), (4, 64, False), (3, 5, False), (6, 21, False),
+                                     (9, 3, False), (2, 45, False), (4, 0, False), (8, 16, True), (5, 11, True),
+                                     (4, 33, True)])
+def test_pieces_at_their_edges(g, P, f32, stats):
+    rng = np.random.default_rng(1000 * g + 10 * P + stats)
+    for n in SIZES:
+        bks = edge_buckets(rng, n)
+        inp = random_inputs(rng, n, g, P)
+        if f32:
+            inp["stale"] = [O.bf16_widen(s) + F32(1e-6) for s in inp["stale"]]
+        announce("pieces g=", g, "P=", P, "f32" if f32 else "bf16", "stats" if stats else "", "n=", n, "buckets",
+                 len(bks))
+        want = O.fused_sync_step(inp["grads"], inp["params"], inp["momentum"], inp["stale"], bks, 0.1, 0.9, 1e-4,
+                                 exchange="f32" if f32 else "bf16")
+        got = run_fused(inp, bks, wd=1e-4, gavg="alias", stats=stats, f32=f32)
+        compare_fused(got, want, f"pieces g={g} P={P} n={n}", gavg=True, stats=stats)
+
+
+@pytest.mark.parametrize("P", [2, 5, 16, 20, 32, 40])
+def test_mean_of_copies_at_its_edges(P):
+    """One staleness 0 for every bucket: the average of the copies, which does not
+    read the parameters (NaN here) it replaces."""
+    rng = np.random.default_rng(70 + P)
+    for n in SIZES:
+        announce("mean P=", P, "n=", n)
+        bks = [(s, k, 0) for s, k, _ in edge_buckets(rng, n)]
+        st = random_inputs(rng, n, 1, P)["stale"]
+        x = np.full(n, np.nan, F32)
+        want, wire = O.global_merge(x, st, bks, pack=True)
+        xd, wd = dev_f32(x), torch.empty(n, dtype=torch.int16, device="cuda")
+        daso.global_merge(xd, [dev_bf16(s) for s in st], bks, wd)
+        torch.cuda.synchronize()
+        check_f32(host_f32(xd), want, f"mean P={P} n={n}")
+        check_u16(host_u16(wd), wire, f"mean wire P={P} n={n}")
+
+
+@pytest.mark.parametrize("nb,n", [(127, 300_001), (129, 300_001), (400, 90_001), (1100, 50_003)])
+def test_statistics_of_more_buckets_than_a_launch(nb, n):
+    """Several launches share one statistics pass; the no-alloc entry point, whose
+    array holds the table of at most 1024 buckets, gives the same bits."""
+    rng = np.random.default_rng(nb)
+    cuts = sorted(rng.choice(np.arange(1, n), nb - 1, replace=False).tolist())
+    edges = [0] + cuts + [n]
+    bks = [(a, b - a, int(rng.choice((1, 2, 4)))) for a, b in zip(edges[:-1], edges[1:])]
+    bks = [bks[i] for i in rng.permutation(nb)]
+    inp = random_inputs(rng, n, 4, 4)
+    announce("statistics of", nb, "buckets, n=", n)
+    want = O.fused_sync_step(inp["grads"], inp["params"], inp["momentum"], inp["stale"], bks, 0.1, 0.9)
+    compare_fused(run_fused(inp, bks), want, f"{nb} buckets")
+    bits = []
+    for noalloc in (False, True):
+        x, m, st = dev_f32(inp["params"]), dev_f32(inp["momentum"]), daso.new_stats(nb)
+        daso.fused_sync_step([dev_f32(a) for a in inp["grads"]], x, m, [dev_bf16(s) for s in inp["stale"]], bks,
+                             0.1, 0.9, stats=st, noalloc=noalloc)
+        torch.cuda.synchronize()
+        check_f32(host_f32(x), want["params"], f"{nb} buckets noalloc={noalloc}")
+        check_stats(daso.decode_stats(st), want["stats"], f"{nb} buckets noalloc={noalloc}")
+        bits.append(st.cpu().numpy().view(np.uint64))
+    assert np.array_equal(bits[0], bits[1])
+
+
+@pytest.mark.parametrize("g,P,S", [(3, 3, 1), (5, 7, 4), (7, 5, 3), (6, 1, 1)])
+def test_division_of_tiny_zero_and_special_values(g, P, S):
+    """Quotients by counts that are no power of two, of values from the smallest
+    subnormal over the 2^-100 below which the plain division is taken to the
+    largest, zeros of both signs, infinities and NaN: correctly rounded."""
+    rng = np.random.default_rng(100 * g + P)
+    n = 40_003
+    announce("division g=", g, "P=", P, "S=", S)
+
+    def values():
+        v = (rng.standard_normal(n) * np.exp2(rng.uniform(-149, 127, n))).astype(F32)
+        v[rng.integers(0, n, 200)] = rng.choice(
+            np.array([0.0, -0.0, np.inf, -np.inf, np.nan, 2.0 ** -149, -2.0 ** -126, 2.0 ** -100], F32), 200)
+        v[:8192] = np.where(np.abs(v[:8192]) < 2.0 ** -90, F32(0.25), v[:8192])  # pieces without tiny values
+        return v
+
+    with np.errstate(all="ignore"):
+        grads = [values()] + [np.zeros(n, F32) for _ in range(g - 1)]
+        stale = [O.bf16_rne(values())] + [np.zeros(n, np.uint16) for _ in range(P - 1)]
+        inp = {"params": np.zeros(n, F32), "momentum": np.zeros(n, F32), "grads": grads, "stale": stale}
+        bks = [(0, n, S)]
+        want = O.fused_sync_step(grads, inp["params"], inp["momentum"], stale, bks, 1e-30, 0.9)
+        got = run_fused(inp, bks, lr=1e-30, gavg="new", stats=False)
+        compare_fused(got, want, f"division g={g} P={P}", gavg=True, stats=False)
