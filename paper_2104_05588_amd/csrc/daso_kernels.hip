@@ -562,7 +562,13 @@ __device__ __forceinline__ int bucket_of(const StepArgs& a, int64_t e) {
 // The sum is latency-bound: each thread issues the loads of up to kLoads
 // partials before it adds them in order.  Missing ones count as zeros, which
 // leaves every sum unchanged (sums of squares are never -0).
-template <int kLoads, int kWaves>
+template <bool SHARED, typename T>
+__device__ __forceinline__ T partial_word(const T& p) {
+  if constexpr (SHARED) return __hip_atomic_load(&p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else return p;
+}
+
+template <int kLoads, bool SHARED, int kWaves>
 __device__ __forceinline__ Acc64 bucket_stats(const SlicePartial* partials, int64_t t0, int64_t t1,
                                               WaveSums<kWaves>& s) {
   constexpr int kThreads = 64 * kWaves;
@@ -572,7 +578,10 @@ __device__ __forceinline__ Acc64 bucket_stats(const SlicePartial* partials, int6
 #pragma unroll
     for (int u = 0; u < kLoads; ++u) {
       const int64_t j = base + u * kThreads;
-      p[u] = j < t1 ? partials[j] : SlicePartial{0.0, 0.0, 0};
+      p[u] = SlicePartial{0.0, 0.0, 0};
+      if (j < t1)
+        p[u] = SlicePartial{partial_word<SHARED>(partials[j].grad_sq), partial_word<SHARED>(partials[j].delta_sq),
+                            partial_word<SHARED>(partials[j].nonfinite)};
     }
 #pragma unroll
     for (int u = 0; u < kLoads; ++u) {
@@ -600,29 +609,32 @@ __device__ __forceinline__ BucketSlots slots_of(const StepArgs& a, int i) {
 }
 
 // A launch of few workgroups sums its statistics in its own last workgroup instead
-// of a second launch.  Each workgroup makes its partials visible to the whole
-// chip (an agent-scope release fence: the XCD's L2 writes them back) and then
-// counts itself done; the one that counts last takes an acquire fence and sums
-// every bucket in the order of stats_kernel (no thread has more than one partial to
-// add, so that the smaller workgroup changes nothing), and sets the
+// of a second launch.  The partials are agent-scope atomic stores, which the
+// hardware completes at the point that all XCDs share; a workgroup waits for its own to
+// complete and then counts itself done, and the one that counts last reads them with
+// agent-scope atomic loads.  So no workgroup needs the release fence, whose write-back of
+// its XCD's L2 (about 0.1 us each, one after the other) is for ordinary stores.
+// The last workgroup sums every bucket in the order of stats_kernel (no thread has more
+// than one partial to add, so that the smaller workgroup changes nothing) and sets the
 // counter back to zero for the next launch.
 template <int SHIFT, int kWaves>
 __device__ __forceinline__ void finish_stats_if_last(const StepArgs& a, WaveSums<kWaves>& s) {
   __shared__ bool last;
-  __syncthreads();  // thread 0 has written this workgroup's partials
-  if (threadIdx.x == 0) {
-    __threadfence();
-    last = atomicAdd(a.done, 1u) == gridDim.x - 1;  // such a launch has one row of workgroups
+  if (threadIdx.x == 0) {  // which stored this workgroup's partials
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0);
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    // such a launch has one row of workgroups
+    last = __hip_atomic_fetch_add(a.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
   }
   __syncthreads();
   if (!last) return;
-  __threadfence();
   for (int i = 0; i < a.nb; ++i) {
     const BucketSlots t = slots_of<SHIFT>(a, i);
-    const Acc64 r = bucket_stats<1>(a.partials, t.first, t.end, s);
+    const Acc64 r = bucket_stats<1, true>(a.partials, t.first, t.end, s);
     if (threadIdx.x == 0) put_stats(a.stats + t.out, r);
   }
-  if (threadIdx.x == 0) atomicExch(a.done, 0u);
+  if (threadIdx.x == 0) __hip_atomic_store(a.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ------------------------------------------------------------------- kernel
@@ -667,7 +679,14 @@ __global__ __launch_bounds__((64 * waves_of<MODE, G, PP, STATS, XF>())) void ste
     const Acc64 t = block_sum(acc, s_sum);
     if (threadIdx.x == 0) {
       const int64_t slot = a.slot0 + slot_of((sbase >> kShift) - a.sb0, b) + (w & 7);
-      a.partials[slot] = SlicePartial{t.gsq, t.dsq, t.nf};
+      SlicePartial* p = a.partials + slot;
+      if (a.done != nullptr) {
+        __hip_atomic_store(&p->grad_sq, t.gsq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&p->delta_sq, t.dsq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&p->nonfinite, t.nf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } else {
+        *p = SlicePartial{t.gsq, t.dsq, t.nf};
+      }
     }
   };
   VecIn<MODE, G, PP, XF> v;
@@ -734,7 +753,7 @@ __global__ __launch_bounds__(kStatsBlock) void stats_kernel(const StatsArgs a) {
   __shared__ WaveSums<kStatsBlock / 64> s_sum;
   const BucketSlots t = a.table[blockIdx.x];
   // 8 loads per thread in flight: a 25 MiB bucket has about 6 partials for each
-  const Acc64 r = bucket_stats<8>(a.partials, t.first, t.end, s_sum);
+  const Acc64 r = bucket_stats<8, false>(a.partials, t.first, t.end, s_sum);
   if (threadIdx.x == 0) put_stats(a.stats + t.out, r);
 }
 
