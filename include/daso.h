@@ -58,9 +58,10 @@
  *    status.  A call may queue more than one kernel: one per 128 buckets of its
  *    table (without statistics, of its runs of buckets of one staleness), one
  *    statistics pass after them (except an eager call of
- *    daso_fused_sync_step over at most 128 slices of 1024 parameters, whose last workgroup sums
- *    its statistics itself; a call being captured into a graph keeps the
- *    pass, as daso_fused_sync_step_noalloc always does), and one zeroing kernel
+ *    daso_fused_sync_step over at most 131,072 parameters, counted in blocks of 8192
+ *    or 16384, whose last workgroup sums its statistics itself; a call being
+ *    captured into a graph keeps the pass, as daso_fused_sync_step_noalloc
+ *    always does), and one zeroing kernel
  *    on the first eager call that uses a new statistics workspace.  If
  *    queueing one of them fails (DASO_EHIP), the kernels queued before it still
  *    run: the outputs (params, momentum, wire, grad_avg, stats) of the buckets

@@ -174,7 +174,9 @@ int64_t fused_cap_override() {
 //  - workgroups of four, with statistics: 4 up to B = 12 (92 us; 95 with 3), 3 up to
 //    36 (g = 4, P = 4: 177 us; 186 with 2, 180 with 4), else 2 (g = 8, P = 0: 204;
 //    219 with 3); unbounded counts as above 3 (478 us; 522 with 2, 501 with 4) or
-//    2 (425; 444 with 3).  g = 4, P = 32 and more are held at 2 or 1 by registers.
+//    2 (425; 444 with 3), and 1 beyond B = 128 (g = 8 with 32 fp32 copies: 745; 817 with
+//    2; registers hold P = 64 there by themselves).
+//  - workgroups of eight: 1.
 //  - workgroups of four, without: 1 (g = 8, P = 32: 473 us against 499 with 2).
 //  - the pack (B = 4) needs the whole chip (24 us; 32 us with 16 wavefronts per CU).
 // A launch of up to 3M elements is not capped: it is over before the front has
@@ -200,9 +202,9 @@ int32_t lds_of(daso::Mode mode, bool with_stats, const daso::Shape& shape, const
     if (unbounded) per_cu = mostly_bf16 ? 10 : 7;
     else if (shape.counts == daso::Counts::kBounded) per_cu = share(300, bytes > 80 ? 5 : 6);
     else per_cu = share(mode == daso::kModeFused ? 190 : 240, 5);
-  } else if (with_stats) {
+  } else if (with_stats && shape.waves == 4) {
     if (unbounded) per_cu = mostly_bf16 ? 3 : 2;
-    else per_cu = bytes <= 12 ? 4 : bytes <= 36 ? 3 : 2;
+    else per_cu = bytes <= 12 ? 4 : bytes <= 36 ? 3 : bytes <= 128 ? 2 : 1;
   }
   return daso::lds_for_workgroups_per_cu(per_cu);
 }
@@ -294,14 +296,13 @@ int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb
   for (int32_t i = 0; i < ranges.size();) {
     const Group g = daso::group_at(ranges, i, shift, room);
     fill_group(a, ranges, g, shift);
-    // an eager launch of few workgroups sums its own statistics in its last
-    // one: that saves a launch's host cost (about 2.6 us) for fences that
-    // cost the GPU about 0.1 us per workgroup; a graph replays launches without
+    // an eager call of few workgroups sums its own statistics in its last one,
+    // which saves a launch's host cost (about 2.6 us); a graph replays launches without
     // that host cost, so a captured call keeps the statistics kernel (counter
     // stays null), and so does the no-alloc entry point, whose scratch every
     // call on the GPU shares: two of its calls racing on another stream could
     // leave a counter wrong for later calls, not only their own statistics
-    a.done = launches == 1 && a.nslices <= daso::kFinishStatsMaxSlices ? counter : nullptr;
+    a.done = launches == 1 && a.nslices * shape.waves <= daso::kFinishStatsMaxWaves ? counter : nullptr;
     const int64_t row = daso::host::launch_grid(a.nslices, 1);
     const dim3 grid(static_cast<uint32_t>(row), static_cast<uint32_t>((std::max<int64_t>(a.nslices, 1) + row - 1) / row));
     if (daso::launch_step(mode, with_stats, a, grid, lds, stream) != hipSuccess) return DASO_EHIP;

@@ -464,7 +464,9 @@ constexpr Counts counts_of() {
 
 // Wavefronts per workgroup.  With statistics 4, which share one partial (one
 // wavefront each took the resnet50-shaped step from 206.7 to 207.4 us and the
-// GPT-shaped one from 6960 to 7120: four times the partials to write and to sum).
+// GPT-shaped one from 6960 to 7120: four times the partials to write and to sum), or 8 for exact
+// counts that take 88 to 128 bytes per element (GPT-shaped 6903 against 7005 us, g = 8
+// with 16 fp32 copies 498 against 504; the resnet50-shaped step would lose, 219 against 213).
 // Without them one, so that a place on a CU is free again as soon as its own loads and
 // stores are done (resnet50-shaped 196 against 204 us, the average of 8 gradients
 // 140 against 145, g = 8 with 12 fp32 copies 406 against 437), except for exact
@@ -474,7 +476,9 @@ template <int MODE, int G, int PP, bool STATS, bool XF>
 constexpr int waves_of() {
   using V = VecIn<MODE, G, PP, XF>;
   constexpr int bytes = 4 * V::kG + (XF ? 4 : 2) * V::kP + (MODE == kModeFused ? 8 : reads_x(MODE) ? 4 : 0);
-  return STATS || (counts_of<MODE, G, PP>() == Counts::kExact && bytes >= 88) ? 4 : 1;
+  constexpr bool heavy = counts_of<MODE, G, PP>() == Counts::kExact && bytes >= 88;
+  if (STATS) return heavy && bytes <= 128 ? 8 : 4;
+  return heavy ? 4 : 1;
 }
 
 // ------------------------------------------------- unbounded run-time counts

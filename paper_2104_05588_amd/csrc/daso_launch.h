@@ -24,13 +24,13 @@ constexpr int32_t kCuLdsBytes = 160 * 1024;  // LDS per CU on gfx950
 // covers the kernel's own few bytes of LDS and the allocation granule.
 inline int32_t lds_for_workgroups_per_cu(int32_t k) { return k >= 1 ? kCuLdsBytes / k - 1024 : 0; }
 
-// An eager fused launch with statistics of at most this many workgroups has its
-// last one sum the statistics (StepArgs::done) instead of a second
-// launch: each of its workgroups pays an agent-scope fence (about 0.1 us of GPU
-// time each), which is cheaper than a launch's host cost for a few dozen
-// workgroups and far dearer for thousands.  Captured calls keep the second
-// launch, whose host cost a graph replay does not pay.
-constexpr int64_t kFinishStatsMaxSlices = 128;
+// An eager fused launch with statistics of at most this many wavefronts (131,072
+// parameters) has its last workgroup sum the statistics (StepArgs::done) instead of
+// a second launch.  The workgroups count themselves done in one counter, at 5 to 11 ns
+// each one after the other: 65,536 parameters (g = 4, P = 2) take 5.2 us against 8.2 in
+// two launches, 200,000 (g = 4, P = 8) 8.0 against 8.2, 300,000 9.7 against 8.2, 2M 35
+// against 20.5.  Captured calls keep the second launch, whose host cost a graph replay does not pay.
+constexpr int64_t kFinishStatsMaxWaves = 512;
 
 // Bytes at the start of a statistics scratch buffer that hold the counter of
 // StepArgs::done (zero whenever no launch is running); the bucket table and the

@@ -35,9 +35,10 @@ enum Mode : int { kModeAvg = 0, kModePack = 1, kModeMerge = 2, kModeFused = 3, k
 // prefetching the next or not.
 constexpr int kVec = 4;            // consecutive elements per lane
 constexpr int kPiece = 64 * kVec;  // elements per wavefront
-// A superblock of 8 workgroups of `waves` wavefronts (1 or 4) holds 8 * waves pieces.
-constexpr int super_shift(int waves) { return waves == 1 ? 11 : 13; }
-static_assert(int64_t(1) << super_shift(1) == 8 * kPiece && int64_t(1) << super_shift(4) == 8 * 4 * kPiece,
+// A superblock of 8 workgroups of `waves` wavefronts (1, 4 or 8) holds 8 * waves pieces.
+constexpr int super_shift(int waves) { return waves == 1 ? 11 : waves == 4 ? 13 : 14; }
+static_assert(int64_t(1) << super_shift(1) == 8 * kPiece && int64_t(1) << super_shift(4) == 8 * 4 * kPiece &&
+                  int64_t(1) << super_shift(8) == 8 * 8 * kPiece,
               "a superblock is the pieces of 8 workgroups");
 
 constexpr int kLaunchBuckets = 128;

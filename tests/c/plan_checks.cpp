@@ -56,7 +56,7 @@ int main() {
       }
       EXPECT(pos == n);
       EXPECT(!with_stats || outs.size() == b.size());
-      for (const int waves : {1, 4}) {
+      for (const int waves : {1, 4, 8}) {
         const int shift = daso::super_shift(waves);
         const int64_t room = rng() % 2 ? INT64_MAX : 8 * static_cast<int64_t>(8 + rng() % 40);
         int64_t hi = 0;
