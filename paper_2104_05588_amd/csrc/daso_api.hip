@@ -89,9 +89,11 @@ int zero_counter_once(Workspace& w, hipStream_t stream) {
 // they read later, so the array never needs clearing.
 // The limit that callers see, DASO_NOALLOC_SCRATCH_BYTES, counts the tiles of the tiled
 // plan, of 2048 or 1024 parameters; the array holds the partials of such a call, which
-// come to one per 1024 parameters, with 64 KB to spare for partials at the edges of
-// buckets.  A call whose buckets need more of those takes more launches.
+// come to one per 1024 parameters, with 64 KB to spare for the partials at a bucket's
+// edges and for the table of a launch.  A call whose buckets need more takes more passes.
 constexpr size_t kScratchBytes = 2 * DASO_NOALLOC_SCRATCH_BYTES + (size_t(64) << 10);
+static_assert(sizeof(SlicePartial) == daso::kPartialBytes && sizeof(BucketSlots) == daso::kEntryBytes,
+              "the sizes that the cut of a call counts with");
 static_assert(kScratchBytes % 256 == 0, "the scratch size is a whole number of 256-byte blocks");
 static __device__ __align__(256) uint64_t scratch[kScratchBytes / sizeof(uint64_t)];
 
@@ -247,22 +249,11 @@ int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb
   const daso::Shape shape = daso::launch_shape(mode, with_stats, a);
   const int shift = daso::super_shift(shape.waves);
   const uint32_t lds = static_cast<uint32_t>(lds_of(mode, with_stats, shape, a, ranges[ranges.size() - 1].end));
-  // statistics scratch: the counter, the bucket table, the partials of every launch of the call
+  // statistics scratch: the counter, the bucket table, the partials
+  const int64_t bytes = space == Space::kFixed ? static_cast<int64_t>(kScratchBytes - daso::kStatsCounterBytes) : INT64_MAX;
+  const daso::Cut cut = daso::cut_of(ranges, shift, with_stats, bytes);
   const size_t table_at = daso::kStatsCounterBytes;
-  const size_t partials_at = table_at + static_cast<size_t>(with_stats ? ranges.size() : 0) * sizeof(BucketSlots);
-  const int64_t room = space == Space::kFixed && with_stats
-                           ? (static_cast<int64_t>(kScratchBytes) - static_cast<int64_t>(partials_at)) /
-                                 static_cast<int64_t>(sizeof(SlicePartial))
-                           : INT64_MAX;
-  int64_t slots = 0, launches = 0;
-  for (int32_t i = 0; i < ranges.size(); ++launches) {
-    const Group g = daso::group_at(ranges, i, shift, room);
-    slots += daso::launch_slots(g, shift);
-    i += g.count;
-  }
-  // one statistics pass for the whole call when the partials of all its launches fit
-  // the scratch, else one after each launch
-  const bool pass_each = slots > room;
+  const size_t partials_at = table_at + static_cast<size_t>(cut.table) * sizeof(BucketSlots);
   std::unique_lock<std::mutex> hold;
   uint32_t* counter = nullptr;
   if (with_stats) {
@@ -278,7 +269,7 @@ int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb
     } else {
       Workspace& w = workspace_entry(dev, stream);
       hold = std::unique_lock<std::mutex>(w.mu);
-      const int rc = reserve(w, partials_at + static_cast<size_t>(slots) * sizeof(SlicePartial));
+      const int rc = reserve(w, partials_at + static_cast<size_t>(cut.slots) * sizeof(SlicePartial));
       if (rc != DASO_OK) return rc;
       base = w.ptr;
       // the last-workgroup statistics of small eager launches count in w's counter
@@ -294,7 +285,7 @@ int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb
   }
   BucketSlots* const table = a.table;
   for (int32_t i = 0; i < ranges.size();) {
-    const Group g = daso::group_at(ranges, i, shift, room);
+    const Group g = daso::group_at(ranges, i, shift, cut.room);
     fill_group(a, ranges, g, shift);
     // an eager call of few workgroups sums its own statistics in its last one,
     // which saves a launch's host cost (about 2.6 us); a graph replays launches without
@@ -302,17 +293,17 @@ int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb
     // stays null), and so does the no-alloc entry point, whose scratch every
     // call on the GPU shares: two of its calls racing on another stream could
     // leave a counter wrong for later calls, not only their own statistics
-    a.done = launches == 1 && a.nslices * shape.waves <= daso::kFinishStatsMaxWaves ? counter : nullptr;
+    a.done = cut.launches == 1 && a.nslices * shape.waves <= daso::kFinishStatsMaxWaves ? counter : nullptr;
     const int64_t row = daso::host::launch_grid(a.nslices, 1);
     const dim3 grid(static_cast<uint32_t>(row), static_cast<uint32_t>((std::max<int64_t>(a.nslices, 1) + row - 1) / row));
     if (daso::launch_step(mode, with_stats, a, grid, lds, stream) != hipSuccess) return DASO_EHIP;
     i += g.count;
     if (!with_stats || a.done != nullptr) continue;
-    if (pass_each || i == ranges.size()) {
-      const int32_t buckets = pass_each ? g.count : ranges.size();
+    if (cut.pass_each || i == ranges.size()) {
+      const int32_t buckets = cut.pass_each ? g.count : ranges.size();
       if (daso::launch_stats(a.partials, table, stats, buckets, stream) != hipSuccess) return DASO_EHIP;
     }
-    if (!pass_each) {
+    if (!cut.pass_each) {
       a.table += g.count;
       a.slot0 += daso::launch_slots(g, shift);
     }

@@ -118,6 +118,34 @@ inline Group group_at(const Ranges& r, int32_t first, int shift, int64_t max_slo
   return g;
 }
 
+// How the statistics of a call lie in a scratch whose first bytes are used: a table of
+// `table` entries, then the partials.  When the partials and table
+// entries of all launches fit, they share one statistics pass.  Else each launch has
+// a pass of its own, reuses the places of the one before and needs a table of kLaunchBuckets
+// entries alone; `room` then limits the partials of a launch.  A launch takes at
+// least one bucket, so the scratch has to hold the partials of the largest.
+constexpr int64_t kPartialBytes = 24, kEntryBytes = 24;
+
+struct Cut {
+  bool pass_each;
+  int64_t table, room, slots, launches;
+};
+
+inline Cut cut_of(const Ranges& r, int shift, bool with_stats, int64_t bytes) {
+  Cut c{false, with_stats ? r.size() : 0, INT64_MAX, 0, 0};
+  for (int32_t i = 0; i < r.size(); ++c.launches) {
+    const Group g = group_at(r, i, shift, c.room);
+    c.slots += launch_slots(g, shift);
+    i += g.count;
+  }
+  if (with_stats && c.slots > (bytes - c.table * kEntryBytes) / kPartialBytes) {
+    c.pass_each = true;
+    c.table = kLaunchBuckets;
+    c.room = (bytes - c.table * kEntryBytes) / kPartialBytes;
+  }
+  return c;
+}
+
 // -------------------------------------------------------------- the tiled plan
 // A coarser decomposition of a fused step, which daso_fused_launch_config
 // reports for tools that time the same streams and in whose tiles the limit of the

@@ -83,6 +83,36 @@ int main() {
       }
     }
   }
+  // The fixed scratch of the no-alloc entry point, with more buckets than its table could
+  // list, the largest bucket that its limit lets pass, or both: every launch's table
+  // and partials stay within it.
+  const int64_t scratch = 2 * static_cast<int64_t>(DASO_NOALLOC_SCRATCH_BYTES) + (int64_t(64) << 10) - 256;
+  const int64_t big = (static_cast<int64_t>(DASO_NOALLOC_SCRATCH_BYTES) - 256 - 260) / 24 * 2048;
+  for (const int64_t large : {int64_t(1), big})
+    for (const int64_t lead : {int64_t(0), int64_t(2047)})
+      for (const int32_t nb : {1, 63, 130, 1100, 2700, 3000, 100000, 1500000}) {
+        std::vector<daso_bucket> b;
+        int64_t pos = 0;
+        if (lead > 0) b.push_back({0, lead, 1, 0}), pos = lead;
+        b.push_back({pos, large - (large > lead ? lead : 0), 2, 0});
+        pos += b.back().numel;
+        while (static_cast<int32_t>(b.size()) < nb) b.push_back({pos++, 1, 1, 0});
+        const daso::Ranges r(b.data(), static_cast<int32_t>(b.size()), true);
+        for (const int waves : {4, 8}) {
+          const int shift = daso::super_shift(waves);
+          const daso::Cut c = daso::cut_of(r, shift, true, scratch);
+          int64_t slots = 0, most = 0;
+          for (int32_t i = 0; i < r.size();) {
+            const daso::Group g = daso::group_at(r, i, shift, c.room);
+            most = std::max(most, daso::launch_slots(g, shift));
+            slots += daso::launch_slots(g, shift);
+            EXPECT(g.count <= c.table);
+            i += g.count;
+          }
+          EXPECT(c.pass_each || (c.table == r.size() && slots == c.slots));
+          EXPECT(c.table * daso::kEntryBytes + (c.pass_each ? most : slots) * daso::kPartialBytes <= scratch);
+        }
+      }
   if (failures == 0) std::puts("plan checks ok");
   return failures == 0 ? 0 : 1;
 }

@@ -81,8 +81,8 @@ def test_mean_of_copies_at_its_edges(P):
 
 @pytest.mark.parametrize("nb,n", [(127, 300_001), (129, 300_001), (400, 90_001), (1100, 50_003)])
 def test_statistics_of_more_buckets_than_a_launch(nb, n):
-    """Several launches share one statistics pass; the no-alloc entry point, whose
-    array holds the table of at most 1024 buckets, gives the same bits."""
+    """Several launches share one statistics pass; the no-alloc entry point gives the
+    same bits."""
     rng = np.random.default_rng(nb)
     cuts = sorted(rng.choice(np.arange(1, n), nb - 1, replace=False).tolist())
     edges = [0] + cuts + [n]
