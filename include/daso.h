@@ -61,7 +61,8 @@
  *    daso_fused_sync_step over at most 131,072 parameters, counted in blocks of 8192
  *    or 16384, whose last workgroup sums its statistics itself; a call being
  *    captured into a graph keeps the pass, as daso_fused_sync_step_noalloc
- *    always does), and one zeroing kernel
+ *    always does, which takes a pass per launch when its array cannot hold the
+ *    partials of all), and one zeroing kernel
  *    on the first eager call that uses a new statistics workspace.  If
  *    queueing one of them fails (DASO_EHIP), the kernels queued before it still
  *    run: the outputs (params, momentum, wire, grad_avg, stats) of the buckets
