@@ -59,7 +59,7 @@ def counter_traffic(workload: str):
 # ------------------------------------------------------- bandwidth ceilings
 class Probes:
     """The access-pattern probes of libdaso_ceiling.so (built by build()): the
-    fused step's loads and stores on its own buffers, tile grid and tile order,
+    fused step's loads and stores on its own buffers, in tiles and a tile order,
     without its arithmetic; and a one-stream copy."""
 
     def __init__(self, torch):
@@ -167,14 +167,14 @@ def copy_rate(torch, probes, reps=10):
 
 
 def ceiling(torch, probes, w, inp, wire, step, reps):
-    """The step and its access pattern on the step's own buffers, tile grid, tile
-    order and occupancy cap, each cold (cache evicted before every call) and warm (back to
+    """The step and its access pattern on the step's own buffers, in the tiles, order
+    and occupancy cap of its tiled plan, each cold (cache evicted before every call) and warm (back to
     back): the reads alone (g + 2 fp32 and P bf16 streams), the writes alone
     (params and momentum fp32, the wire bf16), both mixed as a bare kernel (for the
     g = 4, P = 8 shape also with bf16 at 16 bytes per lane, in two layouts), and
     the separated bound = reads alone + writes alone."""
     n = w.n
-    cfg = step.launch_config()  # the step's own tile size, tile order and occupancy cap
+    cfg = step.launch_config()  # the plan's tile size, tile order and occupancy cap
     tile, run, lds = cfg["tile_elems"], cfg["xcd_run_tiles"], cfg["lds_bytes"]
     it = tile // 1024
     rd32 = list(inp["grads"]) + [inp["params"], inp["momentum"]]

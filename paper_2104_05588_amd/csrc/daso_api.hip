@@ -27,8 +27,8 @@ using daso::SlicePartial;
 
 // ---------------------------------------------------------------- workspace
 // Per (device, stream): the counter of launches that sum their own statistics
-// (kStatsCounterBytes), the per-tile statistics partials of a fused launch and
-// the launch's table of bucket tile ranges.  Allocated on first use and
+// (kStatsCounterBytes), the table of a fused call's buckets and the statistics
+// partials of its workgroups.  Allocated on first use and
 // replaced by one at least twice as large when a larger launch needs it.  A
 // replaced buffer is never freed: launches already queued, and graphs captured
 // earlier, may still use it; the doubling keeps the total within twice the
@@ -221,7 +221,7 @@ int current_device(hipStream_t stream, int* dev) {
   return sdev == *dev ? DASO_OK : DASO_EINVAL;
 }
 
-// Where a fused launch with statistics keeps its tile partials and table.
+// Where a fused launch with statistics keeps its partials and table.
 enum class Space {
   kAllocated,  // the per-(device, stream) workspace, allocated on first use
   kFixed,      // the fixed `scratch` array; calls needing more fail with DASO_ENOSPACE

@@ -1,8 +1,9 @@
 // Bandwidth ceilings of the fused step's memory access pattern, for the bench
 // only (a library of its own, outside the C ABI of include/daso.h).
 //
-// Each probe kernel makes exactly the loads and stores of a fused step, on the
-// same tile grid, tile size and tile order, with the same access widths (16
+// Each probe kernel makes exactly the loads and stores of a fused step, in the
+// tiles and tile order that daso_fused_launch_config reports (coarser than the
+// step's own split), with the same access widths (16
 // bytes per lane for fp32 streams, 8 for bf16) and non-temporal hints, and none
 // of its arithmetic: R32 fp32 and R16 bf16 streams read, W32 fp32 and W16 bf16
 // streams written.  Taking the reads alone, the writes alone and both mixed,

@@ -24,10 +24,10 @@ struct FusedView {
   bool xf32;
 };
 
-// Workgroups of a launch over `ntiles` tiles (one 256-thread workgroup per
-// tile) whose XCD runs are `run` tiles long: one per tile up to kMaxGrid, the
-// largest multiple of the run block (8 * run) within kMaxGrid beyond that, the
-// kernel looping over the remaining tiles.  The dispatch packet counts the grid
+// Workgroups in a row of a launch over `ntiles` slices dealt in runs of `run` per
+// XCD (the step: 1): one per slice up to kMaxGrid, the largest multiple of the run
+// block (8 * run) within kMaxGrid beyond that, where the launch takes further
+// rows.  The dispatch packet counts the grid
 // in work-items in 32 bits, so a grid of 256-thread workgroups must stay below
 // 2^24; kMaxGrid (4096 workgroups per CU) is far above what fills the chip.
 constexpr int64_t kMaxGrid = int64_t(1) << 20;

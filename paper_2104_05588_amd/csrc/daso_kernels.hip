@@ -651,7 +651,7 @@ __device__ __forceinline__ unsigned vec_mask(int64_t e0, int64_t lo, int64_t hi)
   return mask;
 }
 
-// One workgroup per slice (see the work decomposition in daso_launch.h).
+// One workgroup per slice (see the work decomposition in daso_plan.h).
 //
 // The step is bound by HBM: while a wavefront's loads are not in flight, its place
 // on the CU is idle, so everything else is kept off the way to them.  The loads depend
