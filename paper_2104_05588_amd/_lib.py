@@ -134,15 +134,21 @@ def _refuse(t: torch.Tensor, dtypes: Tuple[torch.dtype, ...], n: int, what: str)
     raise ValueError(f"{what} must be contiguous with {n} elements")
 
 
-def _addresses(ts: Sequence[torch.Tensor], dtypes: Tuple[torch.dtype, ...], n: int, what: str,
-               indexed: bool = True) -> List[int]:
+def _addresses(ts: Sequence[Optional[torch.Tensor]], dtypes: Tuple[torch.dtype, ...], n: int, what: str,
+               indexed: bool = True) -> List[Optional[int]]:
     """The device addresses of tensors that must lie on the current device with n
-    contiguous elements of one of `dtypes`.  A call may pass some 70 of them, so the
+    contiguous elements of one of `dtypes`; None is the null pointer, which the C
+    entry point judges.  A call may pass some 70 of them, so the
     checks are the cheapest form of each (get_device is -1 off the device): about
     0.3 us per tensor."""
-    dev = torch.cuda.current_device()
-    out = []
+    dev = None  # looked up once, for the first device tensor
+    out: List[Optional[int]] = []
     for i, t in enumerate(ts):
+        if t is None:
+            out.append(None)
+            continue
+        if dev is None and t.is_cuda:
+            dev = torch.cuda.current_device()
         if t.get_device() != dev or not t.is_cuda or t.dtype not in dtypes or t.numel() != n or not t.is_contiguous():
             _refuse(t, dtypes, n, f"{what}[{i}]" if indexed else what)
         out.append(t.data_ptr())

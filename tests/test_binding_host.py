@@ -1,0 +1,40 @@
+"""The binding's marshalling where no GPU is needed: what it makes of missing
+tensors and of host tensors.  The library is loaded, nothing is launched."""
+import os
+
+import pytest
+import torch
+
+from paper_2104_05588_amd import _lib as L
+from paper_2104_05588_amd import build as B
+
+F32 = (torch.float32,)
+
+
+@pytest.fixture(scope="module")
+def lib():
+    if not os.path.exists(L.LIB_PATH):
+        B.build()
+    return L.load()
+
+
+def test_missing_tensors_are_null_pointers(lib):
+    """None in a list is the null pointer: the C entry points take it for an empty
+    call and refuse it with DASO_EINVAL otherwise."""
+    arr = L._ptr_array([None, None], F32, 0, "grads")
+    assert len(arr) == 2 and arr[0] is None and arr[1] is None
+    assert lib.daso_local_avg(arr, 2, None, 0, None) == L.DASO_OK
+    assert lib.daso_local_avg(arr, 2, 0x1000, 8, None) == L.DASO_EINVAL
+    assert lib.daso_global_merge(None, arr, 2, L.bucket_table([]), 0, None, 0, None) == L.DASO_OK
+
+
+@pytest.mark.parametrize("what,call", [
+    (r"grads\[0\]", lambda t: L.local_avg([t], t)),
+    (r"stale\[0\]", lambda t: L.global_merge(t, [t.to(torch.bfloat16)], [(0, 8, 1)])),
+    ("src", lambda t: L.pack_bf16(t, t)),
+    ("params", lambda t: L.global_merge(t, [], [(0, 8, 1)])),
+])
+def test_host_tensors_are_refused_as_such(lib, what, call):
+    """A host tensor is named in a ValueError, with or without a GPU in the machine."""
+    with pytest.raises(ValueError, match=what + " must be a device tensor"):
+        call(torch.zeros(8))
