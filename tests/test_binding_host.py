@@ -38,3 +38,17 @@ def test_host_tensors_are_refused_as_such(lib, what, call):
     """A host tensor is named in a ValueError, with or without a GPU in the machine."""
     with pytest.raises(ValueError, match=what + " must be a device tensor"):
         call(torch.zeros(8))
+
+
+@pytest.mark.parametrize("nb", [0, 1, 2, 64, 257])
+def test_bucket_table_holds_what_it_is_given(nb):
+    buckets = [(7 * i + (1 << 40), 3 * i, i % 5) for i in range(nb)]
+    arr = L.bucket_table(numpy_rows(buckets))
+    assert len(arr) == max(nb, 1)
+    assert [(b.start, b.numel, b.S, b.reserved) for b in arr] == [(*b, 0) for b in buckets or [(0, 0, 0)]]
+
+
+def numpy_rows(buckets):
+    """The same rows as lists of numpy integers, as a caller may have them."""
+    import numpy as np
+    return [list(np.asarray(b, dtype=np.int64)) for b in buckets]
