@@ -61,7 +61,7 @@
  *    daso_fused_sync_step over at most 131,072 parameters, counted in blocks of 8192
  *    or 16384, whose last workgroup sums its statistics itself; a call being
  *    captured into a graph keeps the pass, as daso_fused_sync_step_noalloc
- *    always does, which takes a pass per launch when its array cannot hold the
+ *    always does; a call takes a pass per launch when the scratch cannot hold the
  *    partials of all), and one zeroing kernel
  *    on the first eager call that uses a new statistics workspace.  If
  *    queueing one of them fails (DASO_EHIP), the kernels queued before it still
@@ -75,7 +75,7 @@
  *    for the fused step.  It never changes a result.
  *  - Calls may be made from several host threads.  Fused steps with statistics
  *    share one small per-(device, stream) workspace (24 bytes per 1024
- *    parameters, plus 216 to 408 bytes per bucket) that the
+ *    parameters, plus 216 to 408 bytes per bucket up to 32 MiB) that the
  *    library allocates on first use (at least 1 MiB), replaces by a larger one
  *    when a larger call needs it, and never frees before the process ends;
  *    calls on one stream are ordered by that stream, and threads may share a

@@ -248,9 +248,12 @@ int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb
   a.g_inv = a.g > 0 ? 1.0f / static_cast<float>(a.g) : 0.0f;
   const daso::Shape shape = daso::launch_shape(mode, with_stats, a);
   const int shift = daso::super_shift(shape.waves);
-  const uint32_t lds = static_cast<uint32_t>(lds_of(mode, with_stats, shape, a, ranges[ranges.size() - 1].end));
+  const int64_t n = ranges[ranges.size() - 1].end;
+  const uint32_t lds = static_cast<uint32_t>(lds_of(mode, with_stats, shape, a, n));
   // statistics scratch: the counter, the bucket table, the partials
-  const int64_t bytes = space == Space::kFixed ? static_cast<int64_t>(kScratchBytes - daso::kStatsCounterBytes) : INT64_MAX;
+  const int64_t least = daso::least_bytes(n);
+  const int64_t bytes = space == Space::kFixed ? static_cast<int64_t>(kScratchBytes - daso::kStatsCounterBytes)
+                                               : least + daso::kSharedBytes;
   const daso::Cut cut = daso::cut_of(ranges, shift, with_stats, bytes);
   const size_t table_at = daso::kStatsCounterBytes;
   const size_t partials_at = table_at + static_cast<size_t>(cut.table) * sizeof(BucketSlots);
@@ -269,7 +272,8 @@ int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb
     } else {
       Workspace& w = workspace_entry(dev, stream);
       hold = std::unique_lock<std::mutex>(w.mu);
-      const int rc = reserve(w, partials_at + static_cast<size_t>(cut.slots) * sizeof(SlicePartial));
+      const int64_t shared = cut.pass_each ? 0 : cut.table * daso::kEntryBytes + cut.slots * daso::kPartialBytes;
+      const int rc = reserve(w, daso::kStatsCounterBytes + static_cast<size_t>(std::max(least, shared)));
       if (rc != DASO_OK) return rc;
       base = w.ptr;
       // the last-workgroup statistics of small eager launches count in w's counter

@@ -126,6 +126,15 @@ inline Group group_at(const Ranges& r, int32_t first, int shift, int64_t max_slo
 // least one bucket, so the scratch has to hold the partials of the largest.
 constexpr int64_t kPartialBytes = 24, kEntryBytes = 24;
 
+// A call's launches share a pass of at most kPassBuckets buckets: it has a workgroup of 1024
+// threads for each, and a dispatch counts its work-items in 32 bits.  In an
+// allocated scratch the shared pass may take kSharedBytes more than a call of so many
+// elements holds anyway (least_bytes), enough for some 150,000 buckets: beyond, a pass
+// each costs some 4 us per 128 buckets, which take 10 to 100 us by themselves, and spares
+// 24 to 28 KB for each 128 of them that would be held for good.
+constexpr int32_t kPassBuckets = 1 << 20;
+constexpr int64_t kSharedBytes = int64_t(32) << 20;
+
 struct Cut {
   bool pass_each;
   int64_t table, room, slots, launches;
@@ -138,12 +147,20 @@ inline Cut cut_of(const Ranges& r, int shift, bool with_stats, int64_t bytes) {
     c.slots += launch_slots(g, shift);
     i += g.count;
   }
-  if (with_stats && c.slots > (bytes - c.table * kEntryBytes) / kPartialBytes) {
+  if (with_stats && (r.size() > kPassBuckets || c.slots > (bytes - c.table * kEntryBytes) / kPartialBytes)) {
     c.pass_each = true;
     c.table = kLaunchBuckets;
     c.room = (bytes - c.table * kEntryBytes) / kPartialBytes;
   }
   return c;
+}
+
+// An allocated scratch holds at least what any one launch over n elements needs, also in
+// the finest split that takes statistics (4 wavefronts per workgroup): 24 bytes per 1024
+// elements and 27 KB.
+inline int64_t least_bytes(int64_t n) {
+  const int64_t slots = launch_slots(Group{0, kLaunchBuckets, 0, n}, super_shift(4));
+  return kLaunchBuckets * kEntryBytes + slots * kPartialBytes;
 }
 
 // -------------------------------------------------------------- the tiled plan
