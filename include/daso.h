@@ -80,7 +80,8 @@
  *    when a larger call needs it, and never frees before the process ends;
  *    calls on one stream are ordered by that stream, and threads may share a
  *    stream (each call queues its kernels together).  A call that allocates
- *    cannot be captured into a HIP graph: make one call of the largest size on
+ *    cannot be captured into a HIP graph: make one call of the largest n (with any
+ *    buckets, g and P) on
  *    the capturing stream before capturing; captured calls then launch kernels
  *    only, and stay valid when later calls enlarge the workspace.  A captured
  *    call keeps the capturing stream's workspace: its replays must not overlap

@@ -251,12 +251,9 @@ int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb
   const int64_t n = ranges[ranges.size() - 1].end;
   const uint32_t lds = static_cast<uint32_t>(lds_of(mode, with_stats, shape, a, n));
   // statistics scratch: the counter, the bucket table, the partials
-  const int64_t least = daso::least_bytes(n);
-  const int64_t bytes = space == Space::kFixed ? static_cast<int64_t>(kScratchBytes - daso::kStatsCounterBytes)
-                                               : least + daso::kSharedBytes;
-  const daso::Cut cut = daso::cut_of(ranges, shift, with_stats, bytes);
-  const size_t table_at = daso::kStatsCounterBytes;
-  const size_t partials_at = table_at + static_cast<size_t>(cut.table) * sizeof(BucketSlots);
+  const int64_t counter_bytes = static_cast<int64_t>(daso::kStatsCounterBytes);
+  daso::Cut cut;
+  if (!with_stats) cut = daso::cut_of(ranges, shift, false, 0);
   std::unique_lock<std::mutex> hold;
   uint32_t* counter = nullptr;
   if (with_stats) {
@@ -269,11 +266,16 @@ int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb
       if (rc != DASO_OK) return rc;
       hold = std::unique_lock<std::mutex>(slot->mu);
       base = slot->ptr;
+      cut = daso::cut_of(ranges, shift, true, static_cast<int64_t>(kScratchBytes) - counter_bytes);
     } else {
       Workspace& w = workspace_entry(dev, stream);
       hold = std::unique_lock<std::mutex>(w.mu);
+      // a captured call cannot allocate: it makes do with what an eager call over as many
+      // elements left, if need be in a pass per launch, which gives the same bits
+      const int64_t least = daso::least_bytes(n), held = static_cast<int64_t>(w.bytes) - counter_bytes;
+      cut = daso::cut_of(ranges, shift, true, capturing && held >= least ? held : least + daso::kSharedBytes);
       const int64_t shared = cut.pass_each ? 0 : cut.table * daso::kEntryBytes + cut.slots * daso::kPartialBytes;
-      const int rc = reserve(w, daso::kStatsCounterBytes + static_cast<size_t>(std::max(least, shared)));
+      const int rc = reserve(w, static_cast<size_t>(counter_bytes + std::max(least, shared)));
       if (rc != DASO_OK) return rc;
       base = w.ptr;
       // the last-workgroup statistics of small eager launches count in w's counter
@@ -283,8 +285,8 @@ int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb
         counter = static_cast<uint32_t*>(base);
       }
     }
-    a.partials = reinterpret_cast<SlicePartial*>(static_cast<char*>(base) + partials_at);
-    a.table = reinterpret_cast<BucketSlots*>(static_cast<char*>(base) + table_at);
+    a.table = reinterpret_cast<BucketSlots*>(static_cast<char*>(base) + counter_bytes);
+    a.partials = reinterpret_cast<SlicePartial*>(a.table + cut.table);
     a.stats = stats;
   }
   BucketSlots* const table = a.table;

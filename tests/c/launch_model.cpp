@@ -246,6 +246,30 @@ static void long_table() {
   EXPECT(allocated <= (size_t(64) << 20));
 }
 
+// A captured call that follows an eager one over as many elements on its stream finds
+// room in the workspace, whatever its buckets and stream counts are: it must not allocate.
+static void capture() {
+  const std::vector<std::vector<daso_bucket>> tables = {
+      even(30000001, 30000001), even(30000001, 6553600), even(30000001, 7001), even(30000001, 261), even(8000000, 97)};
+  int stream = 10;
+  for (const auto& warm : kShapes)
+    for (const auto& shape : kShapes)
+      for (size_t first = 0; first < 4; ++first) {
+        const hipStream_t st = stream_at(stream++);
+        what = "warm-up g=" + std::to_string(warm.first) + " table " + std::to_string(first);
+        EXPECT(run(Call{warm.first, warm.second, tables[first]}, st) == DASO_OK);
+        capturing = true;
+        for (size_t k = 0; k < tables.size(); ++k) {
+          what = "captured g=" + std::to_string(shape.first) + " P=" + std::to_string(shape.second) + " table " +
+                 std::to_string(k) + " after g=" + std::to_string(warm.first) + " table " + std::to_string(first);
+          EXPECT(run(Call{shape.first, shape.second, tables[k]}, st) == DASO_OK);
+        }
+        capturing = false;
+        EXPECT(mallocs_in_capture == 0);
+        mallocs_in_capture = 0;
+      }
+}
+
 int main(int argc, char** argv) {
   if (argc != 3) return 2;
   void* lib = dlopen(argv[1], RTLD_NOW | RTLD_LOCAL);
@@ -255,6 +279,7 @@ int main(int argc, char** argv) {
   const std::string scenario = argv[2];
   if (scenario == "random_tables") random_tables();
   else if (scenario == "long_table") long_table();
+  else if (scenario == "capture") capture();
   else return 2;
   if (failures == 0) std::printf("launch model ok: %d step launches, %d statistics passes\n", steps, passes);
   return failures == 0 ? 0 : 1;

@@ -40,3 +40,7 @@ def test_random_tables(model):
 
 def test_a_long_table_keeps_its_passes_and_its_scratch_bounded(model):
     run(model, "long_table")
+
+
+def test_captured_calls_find_room_after_a_warm_up_of_their_size(model):
+    run(model, "capture")
