@@ -208,9 +208,9 @@ int daso_fused_sync_step(const daso_sync_args* args, hipStream_t stream);
 /* For callers that cannot allocate device memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): daso_fused_sync_step
  * with the same arguments, results and rules, except that the statistics
- * scratch lives in a fixed array in device memory instead of an allocated
- * workspace.  The call never allocates or frees device memory.  Every GPU the library
- * runs on holds its own copy of that array (about 32 MiB) until the process ends; the first
+ * scratch lives in a fixed array of DASO_NOALLOC_SCRATCH_BYTES in device memory instead of
+ * an allocated workspace.  The call never allocates or frees device memory.  Every GPU the library
+ * runs on holds its own copy of that array until the process ends; the first
  * call on a device looks up its address there (that device must be current, as
  * for every call).  All calls of this entry point on one GPU share the array and
  * each leaves its contents behind: calls queued on one stream are ordered by it
@@ -221,7 +221,9 @@ int daso_fused_sync_step(const daso_sync_args* args, hipStream_t stream);
  * the largest number of tiles of 64 consecutive buckets of its table, and one
  * that needs more than DASO_NOALLOC_SCRATCH_BYTES (more than 699,029 tiles: at
  * least about 715 million parameters) returns DASO_ENOSPACE and launches
- * nothing.  Without statistics (stats == NULL) no scratch is used. */
+ * nothing.  The statistics of a bucket of more than 715 million parameters are summed
+ * in parts of that size, so that their last bits may differ from those of
+ * daso_fused_sync_step.  Without statistics (stats == NULL) no scratch is used. */
 #define DASO_NOALLOC_SCRATCH_BYTES ((size_t)16 << 20)
 int daso_fused_sync_step_noalloc(const daso_sync_args* args, hipStream_t stream);
 

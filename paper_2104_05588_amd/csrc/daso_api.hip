@@ -87,11 +87,10 @@ int zero_counter_once(Workspace& w, hipStream_t stream) {
 // kStatsCounterBytes are never used: calls through it keep the statistics
 // kernel (see launch_groups).  The kernels write every partial and table entry
 // they read later, so the array never needs clearing.
-// The limit that callers see, DASO_NOALLOC_SCRATCH_BYTES, counts the tiles of the tiled
-// plan, of 2048 or 1024 parameters; the array holds the partials of such a call, which
-// come to one per 1024 parameters, with 64 KB to spare for the partials at a bucket's
-// edges and for the table of a launch.  A call whose buckets need more takes more passes.
-constexpr size_t kScratchBytes = 2 * DASO_NOALLOC_SCRATCH_BYTES + (size_t(64) << 10);
+// The limit that callers see counts the tiles of the tiled plan, of 2048 or 1024 parameters;
+// the array holds the partials, one per 1024 or 2048 parameters, of one launch at a time
+// or of all, and a bucket that needs more takes several launches.
+constexpr size_t kScratchBytes = DASO_NOALLOC_SCRATCH_BYTES;
 static_assert(sizeof(SlicePartial) == daso::kPartialBytes && sizeof(BucketSlots) == daso::kEntryBytes,
               "the sizes that the cut of a call counts with");
 static_assert(kScratchBytes % 256 == 0, "the scratch size is a whole number of 256-byte blocks");
@@ -120,10 +119,11 @@ int scratch_slot(int dev, ScratchSlot** out) {
 // -------------------------------------------------------------- launching
 // The launch's buckets as kernel arguments.
 void fill_group(StepArgs& a, const Ranges& r, const Group& g, int shift) {
+  a.cont = g.lo > r[g.first].start ? 1 : 0;
   for (int32_t k = 0; k < g.count; ++k) {
     const daso::Range& x = r[g.first + k];
     const int32_t d = 2 * x.S + a.P;
-    a.start[k] = x.start;
+    a.start[k] = k == 0 ? g.lo : x.start;
     a.S[k] = x.S;
     a.inv[k] = d > 0 ? 1.0f / static_cast<float>(d) : 0.0f;
     a.out[k] = x.out;
@@ -290,8 +290,10 @@ int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb
     a.stats = stats;
   }
   BucketSlots* const table = a.table;
+  int64_t from = -1;
   for (int32_t i = 0; i < ranges.size();) {
-    const Group g = daso::group_at(ranges, i, shift, cut.room);
+    const Group g = daso::cut_to(daso::group_at(ranges, i, shift, cut.room, from), shift, cut.room);
+    const bool whole = g.hi == ranges[i + g.count - 1].end;
     fill_group(a, ranges, g, shift);
     // an eager call of few workgroups sums its own statistics in its last one,
     // which saves a launch's host cost (about 2.6 us); a graph replays launches without
@@ -303,7 +305,8 @@ int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb
     const int64_t row = daso::host::launch_grid(a.nslices, 1);
     const dim3 grid(static_cast<uint32_t>(row), static_cast<uint32_t>((std::max<int64_t>(a.nslices, 1) + row - 1) / row));
     if (daso::launch_step(mode, with_stats, a, grid, lds, stream) != hipSuccess) return DASO_EHIP;
-    i += g.count;
+    i += whole ? g.count : 0;
+    from = whole ? -1 : g.hi;
     if (!with_stats || a.done != nullptr) continue;
     if (cut.pass_each || i == ranges.size()) {
       const int32_t buckets = cut.pass_each ? g.count : ranges.size();

@@ -598,7 +598,9 @@ __device__ __forceinline__ Acc64 bucket_stats(const SlicePartial* partials, int6
   return block_sum(v, s);
 }
 
-__device__ __forceinline__ void put_stats(daso_bucket_stats* out, const Acc64& r) {
+__device__ __forceinline__ void put_stats(daso_bucket_stats* stats, const BucketSlots& t, Acc64 r) {
+  daso_bucket_stats* out = stats + t.out;
+  if (t.add) r = Acc64{out->grad_sq + r.gsq, out->delta_sq + r.dsq, out->nonfinite + r.nf};
   out->grad_sq = r.gsq;
   out->delta_sq = r.dsq;
   out->nonfinite = r.nf;
@@ -609,7 +611,8 @@ template <int SHIFT>
 __device__ __forceinline__ BucketSlots slots_of(const StepArgs& a, int i) {
   const int64_t bs = a.start[i], be = a.start[i + 1];
   const int64_t first = a.slot0 + slot_of((bs >> SHIFT) - a.sb0, i);
-  return BucketSlots{first, be > bs ? a.slot0 + slot_of(((be - 1) >> SHIFT) - a.sb0, i) + 8 : first, a.out[i]};
+  return BucketSlots{first, be > bs ? a.slot0 + slot_of(((be - 1) >> SHIFT) - a.sb0, i) + 8 : first, a.out[i],
+                     i == 0 ? a.cont : 0};
 }
 
 // A launch of few workgroups sums its statistics in its own last workgroup instead
@@ -636,7 +639,7 @@ __device__ __forceinline__ void finish_stats_if_last(const StepArgs& a, WaveSums
   for (int i = 0; i < a.nb; ++i) {
     const BucketSlots t = slots_of<SHIFT>(a, i);
     const Acc64 r = bucket_stats<1, true>(a.partials, t.first, t.end, s);
-    if (threadIdx.x == 0) put_stats(a.stats + t.out, r);
+    if (threadIdx.x == 0) put_stats(a.stats, t, r);
   }
   if (threadIdx.x == 0) __hip_atomic_store(a.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -758,7 +761,7 @@ __global__ __launch_bounds__(kStatsBlock) void stats_kernel(const StatsArgs a) {
   const BucketSlots t = a.table[blockIdx.x];
   // 8 loads per thread in flight: a 25 MiB bucket has about 6 partials for each
   const Acc64 r = bucket_stats<8, false>(a.partials, t.first, t.end, s_sum);
-  if (threadIdx.x == 0) put_stats(a.stats + t.out, r);
+  if (threadIdx.x == 0) put_stats(a.stats, t, r);
 }
 
 // Fused instances: compile-time stream counts for the node shapes, g = 4 or 8

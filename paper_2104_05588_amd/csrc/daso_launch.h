@@ -47,7 +47,8 @@ struct SlicePartial {
 // Where stats_kernel finds the partials of a bucket and puts its statistics.
 struct BucketSlots {
   int64_t first, end;
-  int64_t out;
+  int32_t out;
+  int32_t add;  // nonzero: the launch before had the bucket's first elements, whose statistics these are added to
 };
 
 // Kernel arguments, passed by value (3.7 KB).
@@ -78,6 +79,7 @@ struct StepArgs {
   uint32_t flags;
   int32_t xf32;          // nonzero: fp32 exchange (stale copies and wire are fp32)
   int32_t nb;            // buckets in this launch
+  int32_t cont;          // nonzero: the first of them began in the launch before (BucketSlots::add)
   int64_t start[kLaunchBuckets + 1];  // the buckets, sorted and back to back: bucket i is [start[i], start[i + 1])
   int32_t S[kLaunchBuckets];          // staleness of Eq. (1)
   float inv[kLaunchBuckets];          // 1 / (2S + P), rounded to nearest (0 when 2S + P is 0)

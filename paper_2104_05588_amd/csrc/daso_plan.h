@@ -108,8 +108,9 @@ inline int64_t superblocks(int64_t lo, int64_t hi, int shift) {
 // Partials that a launch has places for (slot_of).
 inline int64_t launch_slots(const Group& g, int shift) { return 8 * (superblocks(g.lo, g.hi, shift) + g.count); }
 
-inline Group group_at(const Ranges& r, int32_t first, int shift, int64_t max_slots) {
-  Group g{first, 1, r[first].start, r[first].end};
+// The launch that begins at element `from` (-1: the start) of range `first`.
+inline Group group_at(const Ranges& r, int32_t first, int shift, int64_t max_slots, int64_t from = -1) {
+  Group g{first, 1, from < 0 ? r[first].start : from, r[first].end};
   while (g.count < kLaunchBuckets && first + g.count < r.size()) {
     const Group more{first, g.count + 1, g.lo, r[first + g.count].end};
     if (launch_slots(more, shift) > max_slots) break;
@@ -118,12 +119,19 @@ inline Group group_at(const Ranges& r, int32_t first, int shift, int64_t max_slo
   return g;
 }
 
+// A launch of one range whose partials alone are more than max_slots (at least 16), cut at a
+// superblock so that they fit: the next launch begins where this one ends.
+inline Group cut_to(const Group& g, int shift, int64_t max_slots) {
+  if (launch_slots(g, shift) <= max_slots) return g;
+  return Group{g.first, 1, g.lo, ((g.lo >> shift) + max_slots / 8 - 1) << shift};
+}
+
 // How the statistics of a call lie in a scratch whose first bytes are used: a table of
 // `table` entries, then the partials.  When the partials and table
 // entries of all launches fit, they share one statistics pass.  Else each launch has
 // a pass of its own, reuses the places of the one before and needs a table of kLaunchBuckets
-// entries alone; `room` then limits the partials of a launch.  A launch takes at
-// least one bucket, so the scratch has to hold the partials of the largest.
+// entries alone; `room` then limits the partials of a launch, and a bucket that has more
+// takes several launches (cut_to), whose passes add up its statistics.
 constexpr int64_t kPartialBytes = 24, kEntryBytes = 24;
 
 // A call's launches share a pass of at most kPassBuckets buckets: it has a workgroup of 1024

@@ -62,6 +62,8 @@ static void sum_buckets(const daso::SlicePartial* partials, const daso::BucketSl
       r.nonfinite += partials[j].nonfinite;
     }
     EXPECT(inside(stats + table[i].out, sizeof(r)));
+    const daso_bucket_stats& was = stats[table[i].out];
+    if (table[i].add) r = {was.grad_sq + r.grad_sq, was.delta_sq + r.delta_sq, was.nonfinite + r.nonfinite};
     stats[table[i].out] = r;
   }
 }
@@ -73,7 +75,8 @@ static void model_step(const daso::StepArgs& a, int waves) {
     const int64_t bs = a.start[i], be = a.start[i + 1];
     const int64_t first = a.slot0 + daso::slot_of((bs >> shift) - a.sb0, i);
     EXPECT(inside(a.table + i, sizeof(*a.table)));
-    a.table[i] = daso::BucketSlots{first, be > bs ? a.slot0 + daso::slot_of(((be - 1) >> shift) - a.sb0, i) + 8 : first, a.out[i]};
+    a.table[i] = daso::BucketSlots{first, be > bs ? a.slot0 + daso::slot_of(((be - 1) >> shift) - a.sb0, i) + 8 : first, a.out[i],
+                                   i == 0 ? a.cont : 0};
     for (int64_t sb = bs >> shift; be > bs && sb <= (be - 1) >> shift; ++sb)
       for (int w = 0; w < 8; ++w) {
         int64_t count = 0;
@@ -270,6 +273,36 @@ static void capture() {
       }
 }
 
+// The no-alloc entry point's array, no larger than its documented size, with more partials than it
+// holds: of many buckets, of one bucket, of both.
+static void fixed_array() {
+  const int64_t big = (static_cast<int64_t>(DASO_NOALLOC_SCRATCH_BYTES) - 256 - 260) / 24 * 2048;  // at the limit
+  for (const auto& shape : {std::pair<int, int>{4, 8}, {1, 0}, {9, 40}}) {
+    for (int k = 0; k < 4; ++k) {
+      Call c{shape.first, shape.second, {}, true};
+      int64_t pos = 0;
+      const auto add = [&](int64_t numel) {
+        c.buckets.push_back({pos, numel, 1, 0});
+        pos += numel;
+      };
+      if (k != 1) add(2047);
+      if (k >= 1) add(big - (k == 1 ? 4096 : 80 * 2048));
+      add(0);
+      for (int i = 0; i < (k == 0 ? 170000 : k == 1 ? 0 : 300); ++i) add(1 + i % 3);
+      what = "no-alloc, table " + std::to_string(k) + ", g=" + std::to_string(shape.first);
+      steps = 0;
+      EXPECT(run(c, stream_at(0)) == DASO_OK);
+      EXPECT(k == 0 ? steps >= 170000 / 128 : steps >= 3);
+      if (k == 1) {
+        add(8192);
+        EXPECT(run(c, stream_at(0)) == DASO_ENOSPACE);
+      }
+    }
+  }
+  for (const auto& s : symbol_bytes) EXPECT(s.second <= DASO_NOALLOC_SCRATCH_BYTES);
+  EXPECT(symbol_bytes.size() == 1);
+}
+
 int main(int argc, char** argv) {
   if (argc != 3) return 2;
   void* lib = dlopen(argv[1], RTLD_NOW | RTLD_LOCAL);
@@ -280,6 +313,7 @@ int main(int argc, char** argv) {
   if (scenario == "random_tables") random_tables();
   else if (scenario == "long_table") long_table();
   else if (scenario == "capture") capture();
+  else if (scenario == "fixed_array") fixed_array();
   else return 2;
   if (failures == 0) std::printf("launch model ok: %d step launches, %d statistics passes\n", steps, passes);
   return failures == 0 ? 0 : 1;

@@ -80,13 +80,25 @@ int main() {
           i += g.count;
         }
         EXPECT(hi == n);
+        // with a range cut wherever its partials alone exceed the room
+        int64_t end = 0, from = -1;
+        for (int32_t i = 0; i < r.size();) {
+          const daso::Group g = daso::cut_to(daso::group_at(r, i, shift, room, from), shift, room);
+          EXPECT(g.first == i && g.lo == end && daso::launch_slots(g, shift) <= room);
+          const bool whole = g.hi == r[i + g.count - 1].end;
+          EXPECT(whole || (g.count == 1 && g.hi > g.lo && g.hi < r[i].end && g.hi % (int64_t(1) << shift) == 0));
+          end = g.hi;
+          i += whole ? g.count : 0;
+          from = whole ? -1 : g.hi;
+        }
+        EXPECT(end == n);
       }
     }
   }
   // The fixed scratch of the no-alloc entry point, with more buckets than its table could
   // list, the largest bucket that its limit lets pass, or both: every launch's table
   // and partials stay within it.
-  const int64_t scratch = 2 * static_cast<int64_t>(DASO_NOALLOC_SCRATCH_BYTES) + (int64_t(64) << 10) - 256;
+  const int64_t scratch = static_cast<int64_t>(DASO_NOALLOC_SCRATCH_BYTES) - 256;
   const int64_t big = (static_cast<int64_t>(DASO_NOALLOC_SCRATCH_BYTES) - 256 - 260) / 24 * 2048;
   for (const int64_t large : {int64_t(1), big})
     for (const int64_t lead : {int64_t(0), int64_t(2047)})
@@ -101,13 +113,15 @@ int main() {
         for (const int waves : {4, 8}) {
           const int shift = daso::super_shift(waves);
           const daso::Cut c = daso::cut_of(r, shift, true, scratch);
-          int64_t slots = 0, most = 0;
+          int64_t slots = 0, most = 0, from = -1;
           for (int32_t i = 0; i < r.size();) {
-            const daso::Group g = daso::group_at(r, i, shift, c.room);
+            const daso::Group g = daso::cut_to(daso::group_at(r, i, shift, c.room, from), shift, c.room);
+            const bool whole = g.hi == r[i + g.count - 1].end;
             most = std::max(most, daso::launch_slots(g, shift));
             slots += daso::launch_slots(g, shift);
-            EXPECT(g.count <= c.table);
-            i += g.count;
+            EXPECT(g.count <= c.table && (whole || c.pass_each));
+            i += whole ? g.count : 0;
+            from = whole ? -1 : g.hi;
           }
           EXPECT(c.pass_each || (c.table == r.size() && slots == c.slots));
           EXPECT(c.table * daso::kEntryBytes + (c.pass_each ? most : slots) * daso::kPartialBytes <= scratch);

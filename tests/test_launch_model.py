@@ -44,3 +44,7 @@ def test_a_long_table_keeps_its_passes_and_its_scratch_bounded(model):
 
 def test_captured_calls_find_room_after_a_warm_up_of_their_size(model):
     run(model, "capture")
+
+
+def test_the_fixed_array_keeps_its_size_whatever_the_call(model):
+    run(model, "fixed_array")

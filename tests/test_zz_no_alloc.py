@@ -7,6 +7,7 @@ import pytest
 import torch
 
 import paper_2104_05588_amd as daso
+from oracle import daso_oracle as O
 from workloads import generate as Gen
 from workloads import recipes as R
 
@@ -140,3 +141,74 @@ def test_noalloc_captures_in_a_graph_on_a_fresh_stream():
         assert np.array_equal(m.cpu().numpy().view(np.uint32), want["momentum"]), rep
         assert np.array_equal(wire.cpu().numpy().view(np.uint16), want["wire"]), rep
         assert np.array_equal(stats.cpu().numpy().view(np.uint64), want["stats"]), rep
+
+
+def _device_case(seed, n, g, P):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+
+    def normal(sigma):
+        return torch.randn(n, generator=gen, device="cuda", dtype=torch.float32).mul_(sigma)
+    x = normal(0.02)
+    return {"params": x, "momentum": normal(1e-3), "grads": [normal(1e-3) for _ in range(g)],
+            "stale": [(x + normal(1e-4)).to(torch.bfloat16).view(torch.int16) for _ in range(P)]}
+
+
+def test_noalloc_with_more_buckets_than_its_array_holds():
+    """170,000 buckets of one to three elements: their partials exceed the fixed array
+    and what the allocated workspace shares, so each launch of 128 buckets has a
+    statistics pass of its own, over the places that the one before used.  Both entry
+    points against the oracle, taken once per staleness over the whole set."""
+    starts = np.concatenate([[0], np.cumsum([1 + k % 3 for k in range(170_000)])])
+    n = int(starts[-1])
+    sizes, S = np.diff(starts), np.array([(1, 2, 4)[k % 5 % 3] for k in range(170_000)])
+    bks = [(int(a), int(k), int(s)) for a, k, s in zip(starts, sizes, S)]
+    print(f"\n[case] noalloc, {len(bks)} buckets, n={n}", flush=True)
+    inp = _device_case(21, n, 4, 2)
+    host = {k: [t.cpu().numpy() for t in v] if isinstance(v, list) else v.cpu().numpy() for k, v in inp.items()}
+    stale = [t.view(np.uint16) for t in host["stale"]]
+    gbar = O.local_avg(host["grads"])
+    xl, m = O.sgd_momentum(host["params"], host["momentum"], gbar, 0.1, 0.9, 0.0)
+    each = np.repeat(S, sizes)
+    x = np.choose(np.searchsorted([1, 2, 4], each), [O.merge_eq1(xl, stale, s) for s in (1, 2, 4)])
+    delta = x.astype(np.float64) - xl.astype(np.float64)
+    sums = np.stack([np.add.reduceat(np.square(v), starts[:-1]) for v in (gbar.astype(np.float64), delta)], axis=1)
+    for noalloc in (True, False):
+        got = _run(inp, bks, noalloc=noalloc)
+        assert np.array_equal(got["params"], x.view(np.uint32))
+        assert np.array_equal(got["momentum"], m.view(np.uint32))
+        assert np.array_equal(got["wire"], O.bf16_rne(x))
+        assert not got["stats"][:, 2].any()
+        # at most three squares each, added in another order
+        np.testing.assert_allclose(got["stats"].view(np.float64)[:, :2], sums, rtol=2.0 ** -51, atol=0)
+
+
+def test_noalloc_with_a_bucket_whose_partials_exceed_its_array():
+    """A bucket of 740 million parameters between two others: the array holds the partials of
+    715 million, so the bucket takes two launches whose statistics are added up.
+    Every other output is the same, the statistics up to the order of their sums."""
+    n = 740_000_003
+    bks = [(0, 5_003, 1), (5_003, n - 12_000, 2), (n - 6_997, 6_997, 1)]
+    print(f"\n[case] noalloc, a bucket of {n - 12_000}", flush=True)
+    inp = _device_case(22, n, 1, 0)
+    for nonfinite in (2, 0):
+        inp["grads"][0][n // 2] = float("inf") if nonfinite else 1e-3    # in the first part
+        inp["grads"][0][n - 7_100] = float("nan") if nonfinite else 1e-3  # in the second
+        outs = []
+        for noalloc in (True, False):
+            x, m = inp["params"].clone(), inp["momentum"].clone()
+            stats = daso.new_stats(len(bks))
+            daso.fused_sync_step(inp["grads"], x, m, [], bks, 0.1, 0.9, stats=stats, noalloc=noalloc)
+            torch.cuda.synchronize()
+            outs.append((x, m, daso.decode_stats(stats)))
+        for k in (0, 1):
+            assert torch.equal(outs[0][k].view(torch.int32), outs[1][k].view(torch.int32))
+        for b, (got, want) in enumerate(zip(outs[0][2], outs[1][2])):
+            assert got[2] == want[2] == (nonfinite if b == 1 else 0)
+            if b != 1:
+                assert got == want
+            elif not nonfinite:
+                # 700,000 partials in trees of fewer than 800 additions one after the other: 800 * 2^-53
+                assert 0 < want[0] and abs(got[0] - want[0]) <= 1e-13 * want[0]
+                assert got[1] == want[1] == 0.0  # nothing merged
+        del outs
