@@ -62,7 +62,8 @@
  *    or 16384, whose last workgroup sums its statistics itself; a call being
  *    captured into a graph keeps the pass, as daso_fused_sync_step_noalloc
  *    always does; a call takes a pass per launch when the scratch cannot hold the
- *    partials of all), and one zeroing kernel
+ *    partials of all, and none for launches of small buckets alone, of up to 1024
+ *    parameters or so, which take a workgroup each), and one zeroing kernel
  *    on the first eager call that uses a new statistics workspace.  If
  *    queueing one of them fails (DASO_EHIP), the kernels queued before it still
  *    run: the outputs (params, momentum, wire, grad_avg, stats) of the buckets
@@ -221,8 +222,8 @@ int daso_fused_sync_step(const daso_sync_args* args, hipStream_t stream);
  * the largest number of tiles of 64 consecutive buckets of its table, and one
  * that needs more than DASO_NOALLOC_SCRATCH_BYTES (more than 699,029 tiles: at
  * least about 715 million parameters) returns DASO_ENOSPACE and launches
- * nothing.  The statistics of a bucket of more than 715 million parameters are summed
- * in parts of that size, so that their last bits may differ from those of
+ * nothing.  Over more than 715 million parameters the statistics are summed
+ * in parts of up to that size, so that their last bits may differ from those of
  * daso_fused_sync_step.  Without statistics (stats == NULL) no scratch is used. */
 #define DASO_NOALLOC_SCRATCH_BYTES ((size_t)16 << 20)
 int daso_fused_sync_step_noalloc(const daso_sync_args* args, hipStream_t stream);

@@ -159,6 +159,24 @@ int64_t fused_cap_override() {
   return v;
 }
 
+// The average bucket up to which a launch takes wavefronts of each bucket's own
+// (daso::small_buckets) in place of pieces and superblocks: where they win at every size
+// up to it.  us per call in pieces and in buckets, all of one size:
+//  - with statistics, 1M elements, g = 4, P = 8: buckets of 701 elements 172 and 73, 1001 117 and 56;
+//    g = 8, P = 32: 350 and 114, 234 and 90; g = 4, P = 64: 254 and 168, 181 and 133; but
+//    4M in buckets of 1500, g = 4, P = 64: 364 and 545; of 3001, g = 4, P = 8: 109 and 166;
+//  - with statistics and unbounded counts, g = 9, P = 40: 1001 elements 1084 and 108; 4M in
+//    buckets of 3001 1139 and 325, 4095 674 and 377;
+//  - without, 262144 elements, g = 4, P = 8: 63 elements 251 and 176, 200 60 and 56;
+//    g = 4, P = 64: 462 and 414, 100 229 and 243;
+//  - without, unbounded counts, g = 9, P = 40: 1M in buckets of 701 397 and 124, 1001 287 and 97;
+//    4M in buckets of 2001 647 and 216.
+int64_t small_average_of(bool with_stats, const daso::Shape& shape) {
+  const bool unbounded = shape.counts == daso::Counts::kUnbounded;
+  if (with_stats) return unbounded ? 4096 : 1024;
+  return unbounded ? 2048 : 64;
+}
+
 // LDS per workgroup, which caps how many workgroups share a CU.  By the bytes B
 // that an element is read with; the best caps on MI355X, 25.6M (and, but for the
 // fused step, 70.5M) parameters:
@@ -243,12 +261,14 @@ int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb
   const int drc = current_device(stream, &dev);
   if (drc != DASO_OK) return drc;
   const Ranges ranges(b, nb, with_stats);
+  const int64_t n = ranges[ranges.size() - 1].end;
   if (mode == daso::kModeMerge && a.P > 0 && a.wire == nullptr && ranges.size() == 1 && ranges[0].S == 0)
     mode = daso::kModeMean;
+  a.n = n;
+  for (int32_t r = 0; a.gavg != nullptr && r < a.g; ++r) a.in_place_avg |= a.grads[r] == a.gavg ? 1 : 0;
   a.g_inv = a.g > 0 ? 1.0f / static_cast<float>(a.g) : 0.0f;
   const daso::Shape shape = daso::launch_shape(mode, with_stats, a);
   const int shift = daso::super_shift(shape.waves);
-  const int64_t n = ranges[ranges.size() - 1].end;
   const uint32_t lds = static_cast<uint32_t>(lds_of(mode, with_stats, shape, a, n));
   // statistics scratch: the counter, the bucket table, the partials
   const int64_t counter_bytes = static_cast<int64_t>(daso::kStatsCounterBytes);
@@ -290,7 +310,9 @@ int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb
     a.stats = stats;
   }
   BucketSlots* const table = a.table;
+  const int64_t small_average = small_average_of(with_stats, shape);
   int64_t from = -1;
+  bool partials = false;  // some launch so far leaves its statistics to a pass
   for (int32_t i = 0; i < ranges.size();) {
     const Group g = daso::cut_to(daso::group_at(ranges, i, shift, cut.room, from), shift, cut.room);
     const bool whole = g.hi == ranges[i + g.count - 1].end;
@@ -304,11 +326,15 @@ int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb
     a.done = cut.launches == 1 && a.nslices * shape.waves <= daso::kFinishStatsMaxWaves ? counter : nullptr;
     const int64_t row = daso::host::launch_grid(a.nslices, 1);
     const dim3 grid(static_cast<uint32_t>(row), static_cast<uint32_t>((std::max<int64_t>(a.nslices, 1) + row - 1) / row));
-    if (daso::launch_step(mode, with_stats, a, grid, lds, stream) != hipSuccess) return DASO_EHIP;
+    const int32_t small = daso::small_buckets(ranges, g, small_average);
+    const hipError_t e = small > 0 ? daso::launch_buckets(mode, with_stats, a, small, stream)
+                                   : daso::launch_step(mode, with_stats, a, grid, lds, stream);
+    if (e != hipSuccess) return DASO_EHIP;
+    partials = partials || small == 0;
     i += whole ? g.count : 0;
     from = whole ? -1 : g.hi;
     if (!with_stats || a.done != nullptr) continue;
-    if (cut.pass_each || i == ranges.size()) {
+    if (cut.pass_each ? small == 0 : i == ranges.size() && partials) {
       const int32_t buckets = cut.pass_each ? g.count : ranges.size();
       if (daso::launch_stats(a.partials, table, stats, buckets, stream) != hipSuccess) return DASO_EHIP;
     }

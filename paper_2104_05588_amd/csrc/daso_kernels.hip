@@ -482,6 +482,11 @@ constexpr int waves_of() {
 }
 
 // ------------------------------------------------- unbounded run-time counts
+// How the lanes of a wavefront take the vectors of which `mask` selects elements: kWhole, all are
+// selected; kCut, one by one; kRead, one by one from params and momentum, whose other elements
+// another wavefront may be writing, and whole from the gradients and copies (see whole_reads).
+enum class Lanes { kWhole, kRead, kCut };
+
 template <bool FULL, typename V, typename T>
 __device__ __forceinline__ V get(const T* p, int64_t base, uint32_t off, unsigned mask) {
   if constexpr (FULL) {
@@ -493,6 +498,13 @@ __device__ __forceinline__ V get(const T* p, int64_t base, uint32_t off, unsigne
     __builtin_memcpy(&v, h, sizeof(v));
     return v;
   }
+}
+
+// Whether a piece's gradients and copies may be read as whole vectors whatever elements are
+// selected: none of the vectors reaches past the buffers' n elements, and no gradient is
+// being overwritten with the average.
+__device__ __forceinline__ bool whole_reads(const StepArgs& a, int64_t base) {
+  return a.in_place_avg == 0 && (base + kPiece <= a.n || (a.n & (kVec - 1)) == 0);
 }
 
 // sum + p[0] + p[1] + ...  Streams come in batches, the loads of a batch all
@@ -521,9 +533,10 @@ __device__ __forceinline__ f32x4 add_streams(f32x4 sum, const void* const* p, in
   return sum;
 }
 
-template <int MODE, bool STATS, bool XF, bool FULL>
+template <int MODE, bool STATS, bool XF, Lanes L>
 __device__ __forceinline__ void step_any(const StepArgs& a, int64_t base, uint32_t off, unsigned mask, float two_s,
                                          const Divisor& qg, const Divisor& qm, Acc& acc) {
+  constexpr bool FULL = L == Lanes::kWhole, READ = L != Lanes::kCut;
   f32x4 xl = {0.f, 0.f, 0.f, 0.f};  // (mean) not used: 2S is 0
   f32x4 m = {0.f, 0.f, 0.f, 0.f};
   if constexpr (reads_x(MODE)) xl = get<FULL, f32x4>(a.x, base, off, mask);
@@ -531,7 +544,7 @@ __device__ __forceinline__ void step_any(const StepArgs& a, int64_t base, uint32
   f32x4 gbar = {0.f, 0.f, 0.f, 0.f};
   if constexpr (has_grads(MODE)) {
     // -0 + G_0 == G_0 for every G_0
-    gbar = divide(add_streams<true, FULL>(f32x4{-0.0f, -0.0f, -0.0f, -0.0f},
+    gbar = divide(add_streams<true, READ>(f32x4{-0.0f, -0.0f, -0.0f, -0.0f},
                                           reinterpret_cast<const void* const*>(a.grads), a.g, base, off, mask), qg);
     if (MODE == kModeAvg || a.gavg) put<FULL>(a.gavg, base, off, mask, gbar);
     if constexpr (MODE == kModeAvg) return;
@@ -541,7 +554,7 @@ __device__ __forceinline__ void step_any(const StepArgs& a, int64_t base, uint32
     put<FULL>(a.m, base, off, mask, m);
   }
   f32x4 xn = xl;
-  if (a.P > 0) xn = divide(add_streams<XF, FULL>(merge_start(two_s, xl), a.stale, a.P, base, off, mask), qm);
+  if (a.P > 0) xn = divide(add_streams<XF, READ>(merge_start(two_s, xl), a.stale, a.P, base, off, mask), qm);
   store_results<MODE, STATS, XF, FULL>(a, base, off, mask, gbar, xl, xn, acc);
 }
 
@@ -707,7 +720,7 @@ __global__ __launch_bounds__((64 * waves_of<MODE, G, PP, STATS, XF>())) void ste
       const float two_s = static_cast<float>(2 * a.S[b]);
       Acc acc = {0.0, 0.0, 0u};
       if constexpr (kBatched) finish<MODE, G, PP, XF, STATS, true>(a, base, off, 0xFu, v, two_s, qg, qm, acc);
-      else step_any<MODE, STATS, XF, true>(a, base, off, 0xFu, two_s, qg, qm, acc);
+      else step_any<MODE, STATS, XF, Lanes::kWhole>(a, base, off, 0xFu, two_s, qg, qm, acc);
       if constexpr (kStats) put_partial(b, acc);
       done = true;
     }
@@ -730,7 +743,8 @@ __global__ __launch_bounds__((64 * waves_of<MODE, G, PP, STATS, XF>())) void ste
       const unsigned mask = vec_mask(base + off, a.start[b], a.start[b + 1]);
       if (mask) {
         if constexpr (kBatched) finish<MODE, G, PP, XF, STATS, false>(a, base, off, mask, v, two_s, qg, qm, acc);
-        else step_any<MODE, STATS, XF, false>(a, base, off, mask, two_s, qg, qm, acc);
+        else if (kStats && whole_reads(a, base)) step_any<MODE, STATS, XF, Lanes::kRead>(a, base, off, mask, two_s, qg, qm, acc);
+        else step_any<MODE, STATS, XF, Lanes::kCut>(a, base, off, mask, two_s, qg, qm, acc);
       }
       if constexpr (kStats) {
         put_partial(b, acc);
@@ -744,6 +758,43 @@ __global__ __launch_bounds__((64 * waves_of<MODE, G, PP, STATS, XF>())) void ste
     // for stats_kernel (the grid has at least one workgroup)
     if (w == 0 && threadIdx.x < a.nb) a.table[threadIdx.x] = slots_of<kShift>(a, static_cast<int>(threadIdx.x));
     if (a.done != nullptr) finish_stats_if_last<kShift>(a, s_sum);
+  }
+}
+
+// A launch of small buckets only: with statistics a workgroup of 4 wavefronts for each, which
+// writes the bucket's statistics itself and leaves the statistics pass of the call's other launches an
+// empty entry to add; without, a wavefront for every 256 elements of the largest bucket.
+// step_kernel takes the buckets of a piece (without statistics) or of a superblock one after the
+// other, at 0.4 us each and more with many streams, and a launch of 128 small ones has
+// few of either.
+constexpr int bucket_waves(bool stats) { return stats ? 4 : 1; }
+
+template <int MODE, bool STATS, bool XF>
+__global__ __launch_bounds__(64 * bucket_waves(STATS)) void bucket_kernel(const StepArgs a) {
+  constexpr int kWaves = bucket_waves(STATS);
+  const int i = static_cast<int>(blockIdx.x);
+  const int wave = kWaves == 1 ? static_cast<int>(blockIdx.y) : __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int waves = kWaves == 1 ? static_cast<int>(gridDim.y) : kWaves;
+  const int64_t bs = a.start[i], be = a.start[i + 1];
+  const Divisor qg = make_divisor(a.g, a.g_inv), qm = make_divisor(2 * a.S[i] + a.P, a.inv[i]);
+  const float two_s = static_cast<float>(2 * a.S[i]);
+  const uint32_t off = (threadIdx.x & 63u) * kVec;
+  Acc acc = {0.0, 0.0, 0u};
+  for (int64_t base = (bs & -int64_t(kVec)) + wave * kPiece; base < be; base += waves * kPiece) {
+    const unsigned mask = vec_mask(base + off, bs, be);
+    if (whole_reads(a, base)) {
+      if (mask) step_any<MODE, STATS, XF, Lanes::kRead>(a, base, off, mask, two_s, qg, qm, acc);
+    } else if (mask) {
+      step_any<MODE, STATS, XF, Lanes::kCut>(a, base, off, mask, two_s, qg, qm, acc);
+    }
+  }
+  if constexpr (STATS) {
+    __shared__ WaveSums<kWaves> s_sum;
+    const Acc64 r = block_sum(acc, s_sum);
+    if (threadIdx.x == 0) {
+      put_stats(a.stats, BucketSlots{0, 0, a.out[i], i == 0 ? a.cont : 0}, r);
+      a.table[i] = BucketSlots{0, 0, a.out[i], 1};
+    }
   }
 }
 
@@ -882,6 +933,22 @@ Shape launch_shape(Mode mode, bool with_stats, const StepArgs& a) { return dispa
 
 hipError_t launch_step(Mode mode, bool with_stats, const StepArgs& a, dim3 grid, uint32_t lds, hipStream_t stream) {
   return dispatch(mode, with_stats, a, Launcher{a, grid, lds, stream});
+}
+
+hipError_t launch_buckets(Mode mode, bool with_stats, const StepArgs& a, int32_t waves, hipStream_t stream) {
+  const void* k = nullptr;
+  if (mode == kModeFused && with_stats)
+    k = a.xf32 ? reinterpret_cast<const void*>(&bucket_kernel<kModeFused, true, true>)
+               : reinterpret_cast<const void*>(&bucket_kernel<kModeFused, true, false>);
+  else if (mode == kModeFused)
+    k = a.xf32 ? reinterpret_cast<const void*>(&bucket_kernel<kModeFused, false, true>)
+               : reinterpret_cast<const void*>(&bucket_kernel<kModeFused, false, false>);
+  else
+    k = a.xf32 ? reinterpret_cast<const void*>(&bucket_kernel<kModeMerge, false, true>)
+               : reinterpret_cast<const void*>(&bucket_kernel<kModeMerge, false, false>);
+  void* args[] = {const_cast<StepArgs*>(&a)};
+  const dim3 grid(static_cast<uint32_t>(a.nb), static_cast<uint32_t>(with_stats ? 1 : waves));
+  return hipLaunchKernel(k, grid, dim3(64 * bucket_waves(with_stats)), args, 0, stream);
 }
 
 hipError_t launch_stats(const SlicePartial* partials, const BucketSlots* table, daso_bucket_stats* stats, int32_t nb,

@@ -84,6 +84,8 @@ struct StepArgs {
   int32_t S[kLaunchBuckets];          // staleness of Eq. (1)
   float inv[kLaunchBuckets];          // 1 / (2S + P), rounded to nearest (0 when 2S + P is 0)
   int32_t out[kLaunchBuckets];        // (stats only) index in the caller's table
+  int64_t n;             // elements of the call's buffers
+  int32_t in_place_avg;  // nonzero: gavg is one of the grads
 };
 
 // Arguments of stats_kernel, kept to a few pointers: the host cost of a launch
@@ -108,6 +110,10 @@ Shape launch_shape(Mode mode, bool with_stats, const StepArgs& args);
 // per slice, in rows of 2^kRowShift), each holding `lds` bytes of LDS besides the kernel's own.
 hipError_t launch_step(Mode mode, bool with_stats, const StepArgs& args, dim3 grid, uint32_t lds,
                        hipStream_t stream);
+
+// Enqueue one launch of `mode` (fused, merge) over the buckets in `args`, all small: `waves`
+// wavefronts for each, or with statistics a workgroup, which writes them itself.
+hipError_t launch_buckets(Mode mode, bool with_stats, const StepArgs& args, int32_t waves, hipStream_t stream);
 
 // Enqueue the sums of the statistics of `nb` buckets, whose launches wrote `table` and `partials`.
 hipError_t launch_stats(const SlicePartial* partials, const BucketSlots* table, daso_bucket_stats* stats,

@@ -119,6 +119,16 @@ inline Group group_at(const Ranges& r, int32_t first, int shift, int64_t max_slo
   return g;
 }
 
+// The wavefronts for each bucket of a launch that bucket_kernel takes, as many as the largest
+// bucket has pieces; 0 if it does not: its buckets have at most `average` elements on average
+// and none more than twice that.
+inline int32_t small_buckets(const Ranges& r, const Group& g, int64_t average) {
+  if (g.count < 2 || g.hi - g.lo > average * g.count) return 0;
+  int64_t most = 1;
+  for (int32_t k = g.first; k < g.first + g.count; ++k) most = std::max(most, r[k].end - std::max(r[k].start, g.lo));
+  return most > 2 * average ? 0 : static_cast<int32_t>((most + kVec - 2) / kPiece + 1);
+}
+
 // A launch of one range whose partials alone are more than max_slots (at least 16), cut at a
 // superblock so that they fit: the next launch begins where this one ends.
 inline Group cut_to(const Group& g, int shift, int64_t max_slots) {

@@ -68,6 +68,18 @@ static void sum_buckets(const daso::SlicePartial* partials, const daso::BucketSl
   }
 }
 
+static void model_buckets(const daso::StepArgs& a) {
+  for (int i = 0; i < a.nb && a.stats != nullptr; ++i) {
+    const int64_t count = a.start[i + 1] - a.start[i];
+    EXPECT(inside(a.stats + a.out[i], sizeof(*a.stats)) && inside(a.table + i, sizeof(*a.table)));
+    daso_bucket_stats r = {static_cast<double>(count), 2.0 * static_cast<double>(count), static_cast<uint64_t>(count)};
+    const daso_bucket_stats& was = a.stats[a.out[i]];
+    if (i == 0 && a.cont) r = {was.grad_sq + r.grad_sq, was.delta_sq + r.delta_sq, was.nonfinite + r.nonfinite};
+    a.stats[a.out[i]] = r;
+    a.table[i] = daso::BucketSlots{0, 0, a.out[i], 1};
+  }
+}
+
 static void model_step(const daso::StepArgs& a, int waves) {
   if (a.stats == nullptr) return;
   const int shift = daso::super_shift(waves);
@@ -136,6 +148,11 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
     model_step(a, static_cast<int>(block.x) / 64);
     last_block = block.x;
     last_lds = static_cast<uint32_t>(lds);
+    ++steps;
+  } else if (name.find("bucket_kernel") != std::string::npos) {
+    const daso::StepArgs& a = **reinterpret_cast<daso::StepArgs**>(args);
+    EXPECT(grid.x == static_cast<uint32_t>(a.nb) && (a.stats == nullptr ? block.x == 64 : grid.y == 1 && block.x == 256));
+    model_buckets(a);
     ++steps;
   } else if (name.find("stats_kernel") != std::string::npos) {
     const daso::StatsArgs& a = **reinterpret_cast<daso::StatsArgs**>(args);
@@ -244,7 +261,13 @@ static void random_tables() {
 // dispatch packet, and whose partials would fill a gigabyte.
 static void long_table() {
   what = "4,200,000 buckets of one element";
-  const Call c{4, 2, even(4200000, 1)};
+  Call c{4, 2, even(4200000, 1)};
+  EXPECT(run(c, stream_at(0)) == DASO_OK);
+  for (size_t k = 0, pos = 0; k < c.buckets.size(); ++k) {  // every other launch with a large one
+    c.buckets[k].start = static_cast<int64_t>(pos);
+    c.buckets[k].numel = k % 256 == 5 ? 600 : 1;
+    pos += static_cast<size_t>(c.buckets[k].numel);
+  }
   EXPECT(run(c, stream_at(0)) == DASO_OK);
   EXPECT(allocated <= (size_t(64) << 20));
 }
@@ -288,7 +311,7 @@ static void fixed_array() {
       if (k != 1) add(2047);
       if (k >= 1) add(big - (k == 1 ? 4096 : 80 * 2048));
       add(0);
-      for (int i = 0; i < (k == 0 ? 170000 : k == 1 ? 0 : 300); ++i) add(1 + i % 3);
+      for (int i = 0; i < (k == 0 ? 170000 : k == 1 ? 0 : 300); ++i) add(i % 100 == 7 && i < 80000 ? 1001 : 1 + i % 3);
       what = "no-alloc, table " + std::to_string(k) + ", g=" + std::to_string(shape.first);
       steps = 0;
       EXPECT(run(c, stream_at(0)) == DASO_OK);

@@ -128,3 +128,39 @@ def test_division_of_tiny_zero_and_special_values(g, P, S):
         want = O.fused_sync_step(grads, inp["params"], inp["momentum"], stale, bks, 1e-30, 0.9)
         got = run_fused(inp, bks, lr=1e-30, gavg="new", stats=False)
         compare_fused(got, want, f"division g={g} P={P}", gavg=True, stats=False)
+
+
+@pytest.mark.parametrize("g,P,f32", [(4, 8, False), (1, 0, False), (9, 40, False), (4, 3, True)])
+@pytest.mark.parametrize("stats", [False, True])
+def test_launches_of_small_buckets(g, P, f32, stats):
+    """Launches whose buckets are all small take wavefronts of each bucket's own: buckets of no
+    elements to the most (on average and alone) for each kind of instance and just beyond,
+    in launches by themselves and beside others in one call, whose statistics pass must leave
+    theirs as they are."""
+    rng = np.random.default_rng(31 * g + P + stats)
+    for sizes in ([1] * 300, list(range(0, 130)) * 2, [128, 0] * 65, [129, 1, 1, 1], [2, 1], [64] * 9, [65] * 9,
+                  [2048, 0, 1] * 45, [2049, 1, 1], [4096, 1, 0] * 3, [4097, 1, 1], [8192, 3, 5], [8193, 1, 1, 255],
+                  [40] * 128 + [15000, 7] + [3] * 126 + [257, 1] * 64, [30] * 127 + [9001] + [30] * 200,
+                  [9000, 5, 700, 3, 9000, 4], [9000, 5, 700, 3, 9000, 1, 2]):
+        bks, pos = [], 0
+        for k in sizes:
+            bks.append((pos, k, int(rng.choice((0, 1, 2, 3)))))
+            pos += k
+        inp = random_inputs(rng, pos, g, P)
+        if f32:
+            inp["stale"] = [O.bf16_widen(s) + F32(1e-6) for s in inp["stale"]]
+        announce("small buckets g=", g, "P=", P, "f32" if f32 else "bf16", "stats" if stats else "", "buckets",
+                 len(bks), "n=", pos)
+        order = rng.permutation(len(bks))
+        for table, gavg in ((bks, "alias"), ([bks[i] for i in order], "new")):
+            want = O.fused_sync_step(inp["grads"], inp["params"], inp["momentum"], inp["stale"], table, 0.1, 0.9, 1e-4,
+                                     exchange="f32" if f32 else "bf16")
+            got = run_fused(inp, table, wd=1e-4, gavg=gavg, stats=stats, f32=f32)
+            compare_fused(got, want, f"small buckets g={g} P={P} n={pos}", gavg=True, stats=stats)
+        if not stats and not f32:
+            want, wire = O.global_merge(inp["params"], inp["stale"], bks, pack=True)
+            xd, wd = dev_f32(inp["params"]), torch.empty(pos, dtype=torch.int16, device="cuda")
+            daso.global_merge(xd, [dev_bf16(s) for s in inp["stale"]], bks, wd)
+            torch.cuda.synchronize()
+            check_f32(host_f32(xd), want, f"merge of small buckets P={P} n={pos}")
+            check_u16(host_u16(wd), wire, f"merge wire of small buckets P={P} n={pos}")
