@@ -123,40 +123,48 @@ def _stream_handle(stream: Optional[torch.cuda.Stream]) -> ctypes.c_void_p:
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
-def _refuse(t: torch.Tensor, dtypes: Tuple[torch.dtype, ...], n: int, what: str) -> None:
-    """Raise for a tensor that _ptr does not take."""
+def _checked(t: torch.Tensor, dtypes: Tuple[torch.dtype, ...], n: int, what: str) -> int:
+    """The current device; raises for a tensor that _ptr does not take."""
     if not t.is_cuda:
         raise ValueError(f"{what} must be a device tensor")
-    if t.device.index != torch.cuda.current_device():
-        raise ValueError(f"{what} is on {t.device}, not on the current device cuda:{torch.cuda.current_device()}")
+    dev = torch.cuda.current_device()
+    if t.device.index != dev:
+        raise ValueError(f"{what} is on {t.device}, not on the current device cuda:{dev}")
     if t.dtype not in dtypes:
         raise ValueError(f"{what} must have dtype in {dtypes}, got {t.dtype}")
-    raise ValueError(f"{what} must be contiguous with {n} elements")
+    if t.numel() != n or not t.is_contiguous():
+        raise ValueError(f"{what} must be contiguous with {n} elements")
+    return dev
 
 
-def _addresses(ts: Sequence[Optional[torch.Tensor]], dtypes: Tuple[torch.dtype, ...], n: int, what: str,
-               indexed: bool = True) -> List[Optional[int]]:
+def _addresses(ts: Sequence[Optional[torch.Tensor]], dtypes: Tuple[torch.dtype, ...], n: int,
+               what: str) -> List[Optional[int]]:
     """The device addresses of tensors that must lie on the current device with n
     contiguous elements of one of `dtypes`; None is the null pointer, which the C
     entry point judges.  A call may pass some 70 of them, so the
-    checks are the cheapest form of each (get_device is -1 off the device): about
-    0.3 us per tensor."""
-    dev = None  # looked up once, for the first device tensor
+    checks are the cheapest form of each (get_device is -1 off the device), and a tensor
+    that fails one is looked at again: about 0.3 us per tensor."""
+    # without a device tensor in front the current device is not asked for: there may be none
+    dev = torch.cuda.current_device() if len(ts) and ts[0] is not None and ts[0].is_cuda else None
     out: List[Optional[int]] = []
-    for i, t in enumerate(ts):
-        if t is None:
-            out.append(None)
-            continue
-        if dev is None and t.is_cuda:
-            dev = torch.cuda.current_device()
-        if t.get_device() != dev or not t.is_cuda or t.dtype not in dtypes or t.numel() != n or not t.is_contiguous():
-            _refuse(t, dtypes, n, f"{what}[{i}]" if indexed else what)
+    for t in ts:
+        if (t is None or t.get_device() != dev or not t.is_cuda or t.dtype not in dtypes or t.numel() != n
+                or not t.is_contiguous()):
+            if t is None:
+                out.append(None)
+                continue
+            dev = _checked(t, dtypes, n, f"{what}[{len(out)}]")
         out.append(t.data_ptr())
     return out
 
 
 def _ptr(t: Optional[torch.Tensor], dtypes: Tuple[torch.dtype, ...], n: int, what: str) -> Optional[int]:
-    return None if t is None else _addresses((t,), dtypes, n, what, indexed=False)[0]
+    if t is None:
+        return None
+    if (not t.is_cuda or t.get_device() != torch.cuda.current_device() or t.dtype not in dtypes or t.numel() != n
+            or not t.is_contiguous()):
+        _checked(t, dtypes, n, what)
+    return t.data_ptr()
 
 
 _F32 = (torch.float32,)

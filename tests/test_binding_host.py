@@ -40,6 +40,26 @@ def test_host_tensors_are_refused_as_such(lib, what, call):
         call(torch.zeros(8))
 
 
+@pytest.mark.gpu
+def test_device_tensors_are_checked_one_by_one(lib):
+    """Every wrong tensor of a list or on its own is named with what is wrong, wherever it stands;
+    missing ones are null pointers between device tensors."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    ok, host = torch.zeros(8, device="cuda"), torch.zeros(8)
+    wide, short, strided = ok.double(), ok[:4], torch.zeros(16, device="cuda")[::2]
+    arr = L._ptr_array([None, ok, None, ok], F32, 8, "grads")
+    assert [arr[0], arr[1], arr[2], arr[3]] == [None, ok.data_ptr(), None, ok.data_ptr()]
+    for bad, why in ((host, "must be a device tensor"), (wide, "must have dtype"), (short, "contiguous with 8"),
+                     (strided, "contiguous with 8")):
+        for lst, at in (([bad, ok], 0), ([ok, bad], 1), ([None, bad], 1), ([host if bad is host else ok, ok, bad], 0 if bad is host else 2)):
+            with pytest.raises(ValueError, match=rf"grads\[{at}\] .*{why}"):
+                L._ptr_array(lst, F32, 8, "grads")
+        with pytest.raises(ValueError, match=f"out .*{why}"):
+            L._ptr(bad, F32, 8, "out")
+    assert L._ptr(ok, F32, 8, "out") == ok.data_ptr() and L._ptr(None, F32, 8, "out") is None
+
+
 @pytest.mark.parametrize("nb", [0, 1, 2, 64, 257])
 def test_bucket_table_holds_what_it_is_given(nb):
     buckets = [(7 * i + (1 << 40), 3 * i, i % 5) for i in range(nb)]
