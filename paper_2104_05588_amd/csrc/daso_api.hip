@@ -262,6 +262,8 @@ int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb
   if (drc != DASO_OK) return drc;
   const Ranges ranges(b, nb, with_stats);
   const int64_t n = ranges[ranges.size() - 1].end;
+  // the plain average, in the form that finishes a blocking synchronisation: the wire went
+  // out before it, so a merge that packs one as well keeps the merge's instances
   if (mode == daso::kModeMerge && a.P > 0 && a.wire == nullptr && ranges.size() == 1 && ranges[0].S == 0)
     mode = daso::kModeMean;
   a.n = n;

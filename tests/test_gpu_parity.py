@@ -272,7 +272,7 @@ FUSED_CASES = [
     (10, 50_001, 64, 64, 3, 0.0, 0, "new"),
     (11, 77_777, 4, 16, 5, 0.0, 0, "none"),
     (12, 12_345, 6, 3, 70, 0.0, 0, "none"),
-    # whole blocks of XCD tile runs: 45 streams (runs of 32 tiles), 26 streams (runs of 16)
+    # several superblocks and a part of one: 45 streams (of 16384 elements), 26 streams (of 8192)
     (13, 2 * 256 * 1024 + 4_097, 8, 32, 4, 0.0, 0, "none"),
     (14, 5 * 128 * 1024 + 333, 4, 16, 3, 0.0, 0, "new"),
 ]
@@ -613,7 +613,7 @@ def test_fused_seeded_sweep_over_the_argument_space():
     that select the exact, bounded and run-time-count instances, both exchange
     types, the pre-merge pack flag, the wire, grad_avg and statistics each on or
     off, weight decay, S from 0 to 1000, and 1 to 8 buckets in any order over
-    sizes that span several tiles with ragged tails."""
+    sizes that span several superblocks with ragged tails."""
     rng = np.random.default_rng(2104_05588)
     for case in range(64):
         g = int(rng.choice([1, 2, 3, 4, 4, 5, 8, 8, 12, 16]))
@@ -655,7 +655,7 @@ def test_empty_inputs_launch_nothing():
 
 def test_fused_beyond_int32_element_count():
     """n = 2^31 + 13 elements (g = 1, P = 1, 37 GB of streams): element offsets
-    and tile counts past 32 bits; sampled elements around 2^31 and the ends
+    and rows of workgroups past 32 bits; sampled elements around 2^31 and the ends
     are checked against the oracle one by one."""
     n = (1 << 31) + 13
     announce("fused n =", n)
@@ -695,7 +695,7 @@ def test_fused_step_replays_in_a_hip_graph(n):
     """After a first eager call (which allocates the statistics workspace), the
     fused step can be captured in a graph: every replay, with eager work and
     synchronisations between replays, gives the eager result bit for bit.  The
-    eager call of the small launch (at most 64 tiles) sums its statistics in its
+    eager call of the small launch (at most 131,072 parameters) sums its statistics in its
     last workgroup, the captured one in the statistics kernel: the same bits."""
     rng = np.random.default_rng(77)
     bks = random_buckets(rng, n, 3)
@@ -725,7 +725,7 @@ def test_fused_step_replays_in_a_hip_graph(n):
         if rep == 1:
             # a larger eager call on the same stream enlarges the statistics
             # workspace; the graph keeps using the buffer it captured
-            big = 100_000_000   # 48,829 tiles: more partials than the first 1 MB workspace holds
+            big = 100_000_000   # 97,657 partials: more than the first 1 MB workspace holds
             bx, bm = torch.zeros(big, device="cuda"), torch.zeros(big, device="cuda")
             bg = [torch.zeros(big, device="cuda")]
             with torch.cuda.stream(side):
@@ -805,7 +805,7 @@ def test_earlier_hip_error_is_neither_blamed_nor_consumed():
 
 
 def test_small_and_large_launches_alternate_on_one_stream():
-    """Launches of at most 64 tiles sum their statistics in their last workgroup
+    """Calls of at most 131,072 parameters sum their statistics in their last workgroup
     (a counter in the workspace that each leaves at zero), larger ones in a
     second kernel; mixed on one stream, every call's statistics and outputs
     match the oracle."""
@@ -820,11 +820,9 @@ def test_small_and_large_launches_alternate_on_one_stream():
         compare_fused(got, want, f"alternating launch sizes, call {k} (n = {n})")
 
 
-def test_tile_order_choice_keeps_results_and_a_pending_error():
-    """The first calls of a fused shape alternate between two tile orders and
-    time them with events the library polls: every call gives the same bits,
-    the order it settles on is one of the two, and while a caller's HIP error
-    is pending the polling leaves it in place (neither consumed nor replaced)."""
+def test_repeated_calls_keep_results_and_a_pending_error():
+    """Eight calls in a row of one prepared shape give the same bits, and while a
+    caller's HIP error is pending they leave it in place (neither consumed nor replaced)."""
     import ctypes
     hip = ctypes.CDLL("libamdhip64.so.7")
     hip.hipMalloc.argtypes = [ctypes.POINTER(ctypes.c_void_p), ctypes.c_size_t]
@@ -832,7 +830,7 @@ def test_tile_order_choice_keeps_results_and_a_pending_error():
     for n, use_error in ((1_000_003, False), (1_000_013, True)):
         bks = random_buckets(rng, n, 3)
         inp = random_inputs(rng, n, 4, 16)
-        announce("tile-order choice n=", n, "pending error:", use_error)
+        announce("repeated calls n=", n, "pending error:", use_error)
         grads = [dev_f32(a) for a in inp["grads"]]
         stale = [dev_bf16(a) for a in inp["stale"]]
         x0, m0 = dev_f32(inp["params"]), dev_f32(inp["momentum"])
@@ -842,8 +840,6 @@ def test_tile_order_choice_keeps_results_and_a_pending_error():
         sts = [daso.new_stats(len(bks)) for _ in range(8)]
         steps = [daso.FusedStep(grads, xs[k], ms[k], stale, bks, 0.1, 0.9, 0.0, wire=wires[k], stats=sts[k])
                  for k in range(8)]
-        cfg = steps[0].launch_config()
-        rule = cfg["xcd_run_tiles"]
         torch.cuda.synchronize()
         if use_error:
             ptr = ctypes.c_void_p()
@@ -855,73 +851,60 @@ def test_tile_order_choice_keeps_results_and_a_pending_error():
             assert hip.hipGetLastError() == failed     # still the caller's error
             assert hip.hipGetLastError() == 0
         torch.cuda.synchronize()
-        steps[0]()                                      # polls the samples, now complete
-        torch.cuda.synchronize()
-        chosen = steps[0].launch_config()["xcd_run_tiles"]
-        assert chosen in (rule, 1), (chosen, rule)
         want = O.fused_sync_step(inp["grads"], inp["params"], inp["momentum"], inp["stale"], bks, 0.1, 0.9)
-        for k in range(1, 8):
+        for k in range(8):
             got = {"params": host_f32(xs[k]), "momentum": host_f32(ms[k]), "wire": host_u16(wires[k]),
                    "grad_avg": None, "stats": daso.decode_stats(sts[k])}
-            compare_fused(got, want, f"tile-order choice call {k}")
+            compare_fused(got, want, f"repeated call {k}")
+            assert torch.equal(sts[k].view(torch.int64), sts[0].view(torch.int64))
 
 
-def test_tile_order_samples_on_two_streams_finishing_out_of_order():
-    """After a shape's first call, its six sampled calls alternate between two
-    streams; the first stream is kept busy, so the later samples on the second
-    one finish first.  A call that polls then must not read the unfinished
-    samples' times or leave a HIP error behind; a later poll decides, and every
-    call gives the oracle's bits."""
+def test_calls_on_two_streams_finishing_out_of_order():
+    """Calls of one shape alternate between two streams, of which the first is kept busy,
+    so that later calls on the second finish first: each stream has statistics scratch of its own,
+    every call gives the oracle's bits and none leaves a HIP error behind."""
     import ctypes
     hip = ctypes.CDLL("libamdhip64.so.7")
     rng = np.random.default_rng(919)
     n = 1_000_033
     bks = random_buckets(rng, n, 3)
     inp = random_inputs(rng, n, 4, 16)
-    announce("tile-order samples on two streams, n=", n)
+    announce("calls on two streams, n=", n)
     grads = [dev_f32(a) for a in inp["grads"]]
     stale = [dev_bf16(a) for a in inp["stale"]]
     x0, m0 = dev_f32(inp["params"]), dev_f32(inp["momentum"])
-    sampled = 1 + 6                       # the unsampled first call, then the samples
-    calls = sampled + 2
+    calls = 8
     xs = [x0.clone() for _ in range(calls)]
     ms = [m0.clone() for _ in range(calls)]
     wires = [torch.empty(n, dtype=torch.int16, device="cuda") for _ in range(calls)]
     sts = [daso.new_stats(len(bks)) for _ in range(calls)]
     steps = [daso.FusedStep(grads, xs[k], ms[k], stale, bks, 0.1, 0.9, 0.0, wire=wires[k], stats=sts[k])
              for k in range(calls)]
-    rule = steps[0].launch_config()["xcd_run_tiles"]
     sa, sb = torch.cuda.Stream(), torch.cuda.Stream()
     busy = torch.empty(1 << 29, dtype=torch.float32, device="cuda")   # 2 GiB
     torch.cuda.synchronize()
-    for k in range(sampled):              # odd calls on the first stream, the last sample on the second
+    for k in range(calls):
         s = sa if k % 2 == 1 else sb
         with torch.cuda.stream(s):
             if s is sa:
-                for i in range(6):        # a few ms of fills ahead of each sample on the first stream
+                for i in range(6):        # a few ms of fills ahead of each call on the first stream
                     busy.fill_(float(i))
             steps[k]()
-    sb.synchronize()                      # the second stream's samples are done
-    with torch.cuda.stream(sb):
-        steps[sampled]()                  # polls while the first stream's samples are still queued
+    sb.synchronize()                      # the second stream's calls are done, the first one's are not all
     assert hip.hipPeekAtLastError() == 0
     torch.cuda.synchronize()
-    with torch.cuda.stream(sb):
-        steps[sampled + 1]()              # polls again: every sample has completed
-    torch.cuda.synchronize()
     assert hip.hipGetLastError() == 0
-    assert steps[0].launch_config()["xcd_run_tiles"] in (rule, 1)
     del busy
     want = O.fused_sync_step(inp["grads"], inp["params"], inp["momentum"], inp["stale"], bks, 0.1, 0.9)
     for k in range(calls):
         got = {"params": host_f32(xs[k]), "momentum": host_f32(ms[k]), "wire": host_u16(wires[k]),
                "grad_avg": None, "stats": daso.decode_stats(sts[k])}
-        compare_fused(got, want, f"two-stream sampling call {k}")
+        compare_fused(got, want, f"two-stream call {k}")
 
 
 def test_calls_from_several_host_threads():
     """Four host threads make fused calls with statistics at once, two of them
-    on one shared stream: every call must still see its own tile partials (a
+    on one shared stream: every call must still see its own partials (a
     call's step and statistics pass are queued together)."""
     import threading
     rng = np.random.default_rng(707)
@@ -982,58 +965,53 @@ def test_fused_local_step_only(g):
     compare_fused(got, want, f"local step g={g} bare", wire=False, stats=False)
 
 
-_RUN_ORDER_SCRIPT = r"""
+_CAP_SCRIPT = r"""
+import hashlib
 import sys
-import numpy as np
 import torch
 sys.path.insert(0, sys.argv[1])
 import paper_2104_05588_amd as daso
 torch.cuda.set_device(0)
-n, g, P = 1_200_007, int(sys.argv[2]), int(sys.argv[3])
-bks = [(0, 500_003, 4), (500_003, n - 500_003, 2)]
+n = (3 << 20) + 200_007  # beyond the size up to which a call is not capped by itself
+bks = [(0, 1_500_003, 4), (1_500_003, n - 1_500_003, 2)]
 gen = torch.Generator(device="cuda")
 gen.manual_seed(77)
 x = torch.randn(n, generator=gen, device="cuda") * 0.02
 m = torch.randn(n, generator=gen, device="cuda") * 1e-3
-grads = [torch.randn(n, generator=gen, device="cuda") * 1e-3 for _ in range(g)]
+grads = [torch.randn(n, generator=gen, device="cuda") * 1e-3 for _ in range(9)]
 stale = [(x + torch.randn(n, generator=gen, device="cuda") * 1e-4).to(torch.bfloat16).view(torch.int16)
-         for _ in range(P)]
-outs = []
-for k in range(10):  # after its first call a shape samples two tile orders (6 calls), later ones take the chosen one
-    xk, mk = x.clone(), m.clone()
-    wire = torch.empty(n, dtype=torch.int16, device="cuda")
-    st = daso.new_stats(len(bks))
-    daso.fused_sync_step(grads, xk, mk, stale, bks, 0.1, 0.9, 0.0, wire, None, st)
-    torch.cuda.synchronize()
-    outs.append(np.concatenate([xk.cpu().numpy().view(np.uint8), mk.cpu().numpy().view(np.uint8),
-                                wire.cpu().numpy().view(np.uint8), st.cpu().numpy().ravel().view(np.uint8)]))
-assert all(np.array_equal(o, outs[0]) for o in outs), "calls of one process differ"
-sys.stdout.buffer.write(outs[0].tobytes())
+         for _ in range(32)]
+# workgroups of 4, 8, 4 (bounded counts), 4 (unbounded) wavefronts with statistics, of 1, 4 and 1 without
+for g, P, stats in ((4, 8, True), (8, 32, True), (3, 5, True), (9, 3, True), (4, 8, False), (8, 32, False), (3, 5, False)):
+    for k in range(3):
+        xk, mk = x.clone(), m.clone()
+        wire = torch.empty(n, dtype=torch.int16, device="cuda")
+        st = daso.new_stats(len(bks)) if stats else None
+        daso.fused_sync_step(grads[:g], xk, mk, stale[:P], bks, 0.1, 0.9, 0.0, wire, None, st)
+        torch.cuda.synchronize()
+        h = hashlib.sha256()
+        for t in (xk, mk, wire) + ((st,) if stats else ()):
+            h.update(t.cpu().numpy().tobytes())
+        print(g, P, stats, h.hexdigest(), flush=True)
 """
 
 
-@pytest.mark.parametrize("g,P", [(4, 8), (8, 32)])
-def test_launch_shape_never_changes_a_result(g, P):
-    """DASO_FUSED_RUN_ELEMS, DASO_FUSED_WG_PER_CU and DASO_FUSED_TUNE change only
-    which XCD takes which tiles and how many workgroups share a CU: plain order,
-    the default runs (chosen per shape from the first calls, or not), longer or
-    shorter runs, no occupancy cap and caps of 1 to 3 workgroups per CU all give
-    the same bits (2048- and 1024-element tiles)."""
+def test_occupancy_cap_never_changes_a_result():
+    """DASO_FUSED_WG_PER_CU changes only how many workgroups share a CU: the default, no cap
+    and caps of 1 to 16 give the same bits, for workgroups of 1, 4 and 8 wavefronts and every
+    kind of instance, on every one of three calls."""
     import os
     import subprocess
     import sys
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     outs = {}
-    for run, cap, tune in (("", "", ""), ("0", "0", ""), ("4096", "1", ""), ("65536", "3", ""),
-                           ("1048576", "2", ""), ("", "", "0")):
-        announce("launch shape g=", g, "P=", P, "DASO_FUSED_RUN_ELEMS =", repr(run), "DASO_FUSED_WG_PER_CU =",
-                 repr(cap), "DASO_FUSED_TUNE =", repr(tune))
-        env = dict(os.environ, DASO_FUSED_RUN_ELEMS=run, DASO_FUSED_WG_PER_CU=cap, DASO_FUSED_TUNE=tune)
-        res = subprocess.run([sys.executable, "-c", _RUN_ORDER_SCRIPT, root, str(g), str(P)], capture_output=True,
-                             env=env, timeout=110)
-        assert res.returncode == 0, res.stderr.decode()[-2000:]
-        outs[(run, cap, tune)] = res.stdout
-    base = outs[("", "", "")]
-    assert len(base) > 0
-    for v, o in outs.items():
-        assert o == base, v
+    for cap in ("", "0", "1", "2", "3", "16"):
+        announce("occupancy cap DASO_FUSED_WG_PER_CU =", repr(cap))
+        res = subprocess.run([sys.executable, "-c", _CAP_SCRIPT, root], capture_output=True, text=True,
+                             env=dict(os.environ, DASO_FUSED_WG_PER_CU=cap), timeout=110)
+        assert res.returncode == 0, res.stderr[-2000:]
+        outs[cap] = [ln for ln in res.stdout.splitlines() if ln]
+    assert len(outs[""]) == 21
+    assert all(outs[""][k] == outs[""][k - k % 3] for k in range(21)), "calls of one process differ"
+    for cap, lines in outs.items():
+        assert lines == outs[""], cap

@@ -1,9 +1,9 @@
 """The step's split into pieces of 256 elements at the sizes where it can go
 wrong: around a piece, a superblock of 2048 or 8192 elements and the 16-byte
 vector, with buckets that begin and end inside a piece, several in one piece and
-empty ones, for every kind of instance (exact, bounded and unbounded counts, with one and
-four wavefronts per workgroup, both exchange types); and tables of more buckets than one launch
-takes.  Against the oracle, bit for bit (statistics: fp64 sums in another order,
+empty ones, for every kind of instance (exact, bounded and unbounded counts, with one,
+four and eight wavefronts per workgroup, both exchange types); tables of more buckets than one
+launch takes; and launches of small buckets alone.  Against the oracle, bit for bit (statistics: fp64 sums in another order,
 1e-10)."""
 import numpy as np
 import pytest
@@ -61,22 +61,34 @@ def test_pieces_at_their_edges(g, P, f32, stats):
         compare_fused(got, want, f"pieces g={g} P={P} n={n}", gavg=True, stats=stats)
 
 
-@pytest.mark.parametrize("P", [2, 5, 16, 20, 32, 40])
-def test_mean_of_copies_at_its_edges(P):
-    """One staleness 0 for every bucket: the average of the copies, which does not
-    read the parameters (NaN here) it replaces."""
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("P", [1, 2, 4, 5, 8, 12, 16, 20, 32, 40])
+def test_mean_of_copies_at_its_edges(P, f32):
+    """One staleness 0 for every bucket: the average of the copies, into parameters that
+    are NaN before.  Without a wire, as blocking_average calls it, the instances that do not read the
+    parameters (every exact, bounded and unbounded count); with one, the merge with S = 0."""
     rng = np.random.default_rng(70 + P)
     for n in SIZES:
-        announce("mean P=", P, "n=", n)
+        announce("mean P=", P, "f32" if f32 else "bf16", "n=", n)
         bks = [(s, k, 0) for s, k, _ in edge_buckets(rng, n)]
         st = random_inputs(rng, n, 1, P)["stale"]
+        if f32:
+            st = [O.bf16_widen(s) + F32(1e-6) for s in st]
         x = np.full(n, np.nan, F32)
-        want, wire = O.global_merge(x, st, bks, pack=True)
-        xd, wd = dev_f32(x), torch.empty(n, dtype=torch.int16, device="cuda")
-        daso.global_merge(xd, [dev_bf16(s) for s in st], bks, wd)
+        want, wire = O.global_merge(x, st, bks, pack=True, exchange="f32" if f32 else "bf16")
+        sd = [(dev_f32 if f32 else dev_bf16)(s) for s in st]
+        xd = dev_f32(x)
+        daso.global_merge(xd, sd, bks)
         torch.cuda.synchronize()
         check_f32(host_f32(xd), want, f"mean P={P} n={n}")
-        check_u16(host_u16(wd), wire, f"mean wire P={P} n={n}")
+        xd, wd = dev_f32(x), torch.empty(n, dtype=torch.float32 if f32 else torch.int16, device="cuda")
+        daso.global_merge(xd, sd, bks, wd)
+        torch.cuda.synchronize()
+        check_f32(host_f32(xd), want, f"merge with S = 0, P={P} n={n}")
+        if f32:
+            check_f32(host_f32(wd), wire, f"wire of a merge with S = 0, P={P} n={n}")
+        else:
+            check_u16(host_u16(wd), wire, f"wire of a merge with S = 0, P={P} n={n}")
 
 
 @pytest.mark.parametrize("nb,n", [(127, 300_001), (129, 300_001), (400, 90_001), (1100, 50_003)])
@@ -164,3 +176,44 @@ def test_launches_of_small_buckets(g, P, f32, stats):
             torch.cuda.synchronize()
             check_f32(host_f32(xd), want, f"merge of small buckets P={P} n={pos}")
             check_u16(host_u16(wd), wire, f"merge wire of small buckets P={P} n={pos}")
+
+
+def test_captured_call_of_more_buckets_than_its_warm_up():
+    """An eager call with one bucket warms the stream up; the captured one has 3000, whose
+    partials and table exceed the workspace, so its launches take a statistics pass each.
+    Every replay, with eager work between, gives the bits of an eager call with them."""
+    n, size = 20_000_001, 6_667
+    bks = [(s, min(size, n - s), 1 + s // size % 3) for s in range(0, n, size)]
+    announce("captured", len(bks), "buckets after one, n=", n)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    x0 = torch.randn(n, generator=gen, device="cuda") * 0.02
+    m0 = torch.randn(n, generator=gen, device="cuda") * 1e-3
+    grads = [torch.randn(n, generator=gen, device="cuda") * 1e-3 for _ in range(2)]
+    stale = [(x0 + 1e-4).to(torch.bfloat16) for _ in range(3)]
+    x, m = x0.clone(), m0.clone()
+    one, stats = daso.new_stats(1), daso.new_stats(len(bks))
+    step = daso.FusedStep(grads, x, m, stale, bks, 0.1, 0.9, stats=stats)
+    step()                                             # on another stream
+    torch.cuda.synchronize()
+    eager = (x.clone(), m.clone(), stats.clone())
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        daso.fused_sync_step(grads, x, m, stale, [(0, n, 1)], 0.1, 0.9, stats=one)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        step()
+    for rep in range(3):
+        x.copy_(x0)
+        m.copy_(m0)
+        stats.fill_(-1.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(x.view(torch.int32), eager[0].view(torch.int32)), rep
+        assert torch.equal(m.view(torch.int32), eager[1].view(torch.int32)), rep
+        assert torch.equal(stats.view(torch.int64), eager[2].view(torch.int64)), rep
+        with torch.cuda.stream(side):                  # other work in the same workspace
+            daso.fused_sync_step(grads, x, m, stale, [(0, n, 1)], 0.1, 0.9, stats=one)
+        torch.cuda.synchronize()
