@@ -69,11 +69,13 @@
  *    run: the outputs (params, momentum, wire, grad_avg, stats) of the buckets
  *    they cover may then already be updated, the others are untouched.
  *  - Launch shape: a wavefront takes 256 consecutive parameters, and neighbouring
- *    ones are dealt to the XCDs in turn; workgroups hold LDS that they do not use, so
- *    that only as many share a CU as have about 60 to 100 KB of loads in
- *    flight (measured best on MI355X).  The environment variable
+ *    ones are dealt to the XCDs in turn; in calls over more than 3M parameters workgroups hold
+ *    LDS that they do not use, which caps how many share a CU (measured best on
+ *    MI355X, by the bytes that a parameter is read with).  The environment variable
  *    DASO_FUSED_WG_PER_CU (0 = no cap), read once per process, replaces the count
- *    for the fused step.  It never changes a result.
+ *    for the fused step.  It never changes a result.  (DASO_FUSED_RUN_ELEMS acts on
+ *    daso_fused_launch_config alone, and DASO_FUSED_TUNE, which chose between two
+ *    orders of tiles, on nothing any more.)
  *  - Calls may be made from several host threads.  Fused steps with statistics
  *    share one small per-(device, stream) workspace (24 bytes per 1024
  *    parameters, plus 216 to 408 bytes per bucket up to 32 MiB) that the

@@ -306,8 +306,9 @@ class FusedStep:
         self._fn = getattr(load(), self._name)
 
     def launch_config(self) -> dict:
-        """The launch shape of this call (daso_fused_launch_config): elements per
-        tile, tiles of the first launch, tiles per XCD run, LDS per workgroup."""
+        """The tiled plan of this call (daso_fused_launch_config), in whose tiles the limit of
+        the no-alloc entry point is stated: elements per tile, tiles of the first 64
+        buckets, tiles per XCD run, LDS per workgroup.  The step runs in a finer split."""
         c = daso_launch_config()
         _check(load().daso_fused_launch_config(self._byref, ctypes.byref(c)), "daso_fused_launch_config")
         return {f: getattr(c, f) for f, _ in daso_launch_config._fields_}

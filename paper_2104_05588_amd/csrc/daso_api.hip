@@ -248,20 +248,22 @@ enum class Space {
 int launch_groups(daso::Mode mode, StepArgs& a, const daso_bucket* b, int32_t nb,
                   daso_bucket_stats* stats, hipStream_t stream, Space space) {
   const bool with_stats = (mode == daso::kModeFused) && stats != nullptr;
-  const int64_t tile = daso::plan_tile(mode, a.g, a.P, a.xf32 != 0);
-  int64_t max_tiles = 1;
-  for (int32_t i = 0; i < nb; i += daso::kPlanBuckets) {
-    const int64_t tiles = daso::plan_tiles(b, nb, i, tile);
-    if (tiles > INT32_MAX) return DASO_EINVAL;
-    max_tiles = std::max(max_tiles, tiles);
+  const Ranges ranges(b, nb, with_stats);
+  const int64_t n = ranges[ranges.size() - 1].end;
+  // The limits that are stated in tiles: of the no-alloc entry point's scratch, and 2^31 of them
+  // for 64 buckets, which fewer than 2^40 elements cannot reach.
+  if ((with_stats && space == Space::kFixed) || n >= int64_t(1) << 40) {
+    const int64_t tile = daso::plan_tile(mode, a.g, a.P, a.xf32 != 0);
+    int64_t max_tiles = 1;
+    for (int32_t i = 0; i < nb; i += daso::kPlanBuckets)
+      max_tiles = std::max(max_tiles, daso::plan_tiles(b, nb, i, tile));
+    if (max_tiles > INT32_MAX) return DASO_EINVAL;
+    if (with_stats && space == Space::kFixed && daso::plan_scratch(max_tiles) > DASO_NOALLOC_SCRATCH_BYTES)
+      return DASO_ENOSPACE;
   }
-  if (with_stats && space == Space::kFixed && daso::plan_scratch(max_tiles) > DASO_NOALLOC_SCRATCH_BYTES)
-    return DASO_ENOSPACE;
   int dev = 0;
   const int drc = current_device(stream, &dev);
   if (drc != DASO_OK) return drc;
-  const Ranges ranges(b, nb, with_stats);
-  const int64_t n = ranges[ranges.size() - 1].end;
   // the plain average, in the form that finishes a blocking synchronisation: the wire went
   // out before it, so a merge that packs one as well keeps the merge's instances
   if (mode == daso::kModeMerge && a.P > 0 && a.wire == nullptr && ranges.size() == 1 && ranges[0].S == 0)
@@ -439,8 +441,6 @@ int fused_args(const daso_sync_args* args, StepArgs& a) {
   if (s.n == 0) return DASO_OK;
   for (int32_t r = 0; r < s.g; ++r) a.grads[r] = s.grads[r];
   for (int32_t i = 0; i < s.P; ++i) a.stale[i] = v.stale[i];
-  a.g = s.g;
-  a.P = s.P;
   a.x = s.params;
   a.m = s.momentum;
   a.wire = v.wire;
