@@ -59,7 +59,7 @@ def counter_traffic(workload: str):
 # ------------------------------------------------------- bandwidth ceilings
 class Probes:
     """The access-pattern probes of libdaso_ceiling.so (built by build()): the
-    fused step's loads and stores on its own buffers, in tiles and a tile order,
+    fused step's loads and stores on its own buffers, in the step's pieces or in tiles,
     without its arithmetic; and a one-stream copy."""
 
     def __init__(self, torch):
@@ -155,55 +155,77 @@ def time_warm(torch, fn, reps):
     return a.elapsed_time(b) * 1e3 / reps
 
 
-def copy_rate(torch, probes, reps=10):
-    """A 1 GiB device copy by the probe library's copy kernel (16 bytes per lane,
-    plain tile order), back to back: read plus written bytes per second."""
+def copy_rate(torch, probes, reps=10, form=2):
+    """A 1 GiB device copy by the probe library's copy kernels (16 bytes per lane; form 2:
+    2048-element tiles in plain order, 4: the step's pieces), back to back: read plus
+    written bytes per second."""
     n = 1 << 28
     src = torch.empty(n, dtype=torch.float32, device="cuda").fill_(1.0)
     dst = torch.empty_like(src)
-    us = time_warm(torch, probes.call([src], [], [dst], [], n, 2, 1), reps)
+    us = time_warm(torch, probes.call([src], [], [dst], [], n, form, 1), reps)
     del src, dst
     return 2 * 4 * n / (us * 1e-6) / 1e9
 
 
-def ceiling(torch, probes, w, inp, wire, step, reps):
-    """The step and its access pattern on the step's own buffers, in the tiles, order
-    and occupancy cap of its tiled plan, each cold (cache evicted before every call) and warm (back to
-    back): the reads alone (g + 2 fp32 and P bf16 streams), the writes alone
-    (params and momentum fp32, the wire bf16), both mixed as a bare kernel (for the
-    g = 4, P = 8 shape also with bf16 at 16 bytes per lane, in two layouts), and
-    the separated bound = reads alone + writes alone."""
-    n = w.n
-    cfg = step.launch_config()  # the plan's tile size, tile order and occupancy cap
-    tile, run, lds = cfg["tile_elems"], cfg["xcd_run_tiles"], cfg["lds_bytes"]
-    it = tile // 1024
-    rd32 = list(inp["grads"]) + [inp["params"], inp["momentum"]]
-    rd16 = list(inp["stale"])
-    wr32, wr16 = [inp["params"], inp["momentum"]], [wire]
-    read_b = n * (4 * len(rd32) + 2 * len(rd16))
-    write_b = n * 10
+def step_split(g, P):
+    """Wavefronts per workgroup, and LDS bytes that cap how many share a CU, of a fused
+    step with statistics, exact counts (g = 4 or 8, P = 2 to 32 in bf16) and more than 3M
+    parameters: what the library launches, for the probes of the step's access pattern."""
+    read = 4 * g + 2 * P + 8
+    waves = 8 if 88 <= read <= 128 else 4
+    per_cu = 1 if waves == 8 or read > 128 else 4 if read <= 12 else 3 if read <= 36 else 2
+    return waves, 160 * 1024 // per_cu - 1024
+
+
+def pattern_streams(inp, wire):
+    """The streams that a step reads and writes: fp32 and bf16 read, fp32 and bf16 written."""
+    return (list(inp["grads"]) + [inp["params"], inp["momentum"]], list(inp["stale"]),
+            [inp["params"], inp["momentum"]], [wire])
+
+
+def time_both(torch, fns, reps):
+    """Each callable cold (cache evicted before every call) and warm (back to back)."""
     scratch = torch.empty(1 << 28, dtype=torch.float32, device="cuda")
-    fns = {"step": step,
-           "reads_alone": probes.call(rd32, rd16, [], [], n, it, run, lds),
-           "writes_alone": probes.call([], [], wr32, wr16, n, it, run, lds),
-           "bare_mix": probes.call(rd32, rd16, wr32, wr16, n, it, run, lds)}
-    if (len(rd32), len(rd16)) == (6, 8) and tile == 2048 and n % 8 == 0:
-        # the same mix with bf16 at 16 bytes per lane: each lane its own 8 elements
-        # (fp32 at a 32-byte lane stride), and fp32 left as the step takes it
-        fns["bare_mix_8_per_lane"] = probes.call(rd32, rd16, wr32, wr16, n, 0, run, lds)
-        fns["bare_mix_bf16_16B"] = probes.call(rd32, rd16, wr32, wr16, n, -1, run, lds)
-    out = {"tile_elems": tile, "xcd_run_tiles": run, "lds_bytes": lds, "read_bytes": read_b,
-           "write_bytes": write_b}
+    out = {}
     for name, fn in fns.items():
         med, mn = time_cold(torch, fn, reps, scratch)
         out[name] = {"cold_median_us": med, "cold_min_us": mn, "warm_us": time_warm(torch, fn, reps)}
-    del scratch
-    for name, b in (("reads_alone", read_b), ("writes_alone", write_b), ("bare_mix", read_b + write_b),
-                    ("bare_mix_8_per_lane", read_b + write_b), ("bare_mix_bf16_16B", read_b + write_b),
-                    ("step", read_b + write_b)):
-        if name not in out:
-            continue
-        out[name]["cold_GBps"] = b / (out[name]["cold_median_us"] * 1e-6) / 1e9
+    return out
+
+
+def add_rates(out, read_b, write_b):
+    for name, t in out.items():
+        b = read_b if name == "reads_alone" else write_b if name == "writes_alone" else read_b + write_b
+        t["cold_GBps"] = b / (t["cold_median_us"] * 1e-6) / 1e9
+
+
+def ceiling(torch, probes, w, inp, wire, step, reps):
+    """The step and its access pattern on the step's own buffers, in the step's pieces
+    and under its occupancy cap, each cold and warm: the reads alone (g + 2 fp32 and P
+    bf16 streams), the writes alone
+    (params and momentum fp32, the wire bf16), both mixed as a bare kernel, and
+    the separated bound = reads alone + writes alone.  Beside them the mix in the
+    tiles, order and cap of daso_fused_launch_config (for the g = 4, P = 8 shape also
+    with bf16 at 16 bytes per lane, in two layouts)."""
+    n = w.n
+    waves, lds = step_split(w.g, w.P)
+    rd32, rd16, wr32, wr16 = pattern_streams(inp, wire)
+    read_b = n * (4 * len(rd32) + 2 * len(rd16))
+    write_b = n * 10
+    cfg = step.launch_config()
+    tile, run, tile_lds = cfg["tile_elems"], cfg["xcd_run_tiles"], cfg["lds_bytes"]
+    fns = {"step": step,
+           "reads_alone": probes.call(rd32, rd16, [], [], n, waves, 1, lds),
+           "writes_alone": probes.call([], [], wr32, wr16, n, waves, 1, lds),
+           "bare_mix": probes.call(rd32, rd16, wr32, wr16, n, waves, 1, lds),
+           "tiled_mix": probes.call(rd32, rd16, wr32, wr16, n, tile // 1024, run, tile_lds)}
+    if (len(rd32), len(rd16)) == (6, 8) and tile == 2048 and n % 8 == 0:
+        # the tiled mix with bf16 at 16 bytes per lane: each lane its own 8 elements
+        # (fp32 at a 32-byte lane stride), and fp32 left at 16 bytes next to each other
+        fns["tiled_mix_8_per_lane"] = probes.call(rd32, rd16, wr32, wr16, n, 0, run, tile_lds)
+        fns["tiled_mix_bf16_16B"] = probes.call(rd32, rd16, wr32, wr16, n, -1, run, tile_lds)
+    out = time_both(torch, fns, reps)
+    add_rates(out, read_b, write_b)
     sep = out["reads_alone"]["cold_median_us"] + out["writes_alone"]["cold_median_us"]
     sep_warm = out["reads_alone"]["warm_us"] + out["writes_alone"]["warm_us"]
     out["separated_bound_cold_us"] = sep
@@ -211,6 +233,8 @@ def ceiling(torch, probes, w, inp, wire, step, reps):
     out["step_cold_over_separated"] = sep / out["step"]["cold_median_us"]
     out["separated_bound_warm_us"] = sep_warm
     out["step_warm_over_separated"] = sep_warm / out["step"]["warm_us"]
+    out.update({"wavefronts_per_workgroup": waves, "lds_bytes": lds, "tile_elems": tile, "xcd_run_tiles": run,
+                "tile_lds_bytes": tile_lds, "read_bytes": read_b, "write_bytes": write_b})
     return out
 
 
@@ -220,30 +244,22 @@ def phased(torch, probes, w, inp, wire, step, reps):
     meet again) beside the bare mix, the reads alone and the writes alone, on
     the step's own buffers, cold and warm."""
     n = w.n
+    waves, lds = step_split(w.g, w.P)
+    rd32, rd16, wr32, wr16 = pattern_streams(inp, wire)
     it = step.launch_config()["tile_elems"] // 1024
-    rd32 = list(inp["grads"]) + [inp["params"], inp["momentum"]]
-    rd16 = list(inp["stale"])
-    wr32, wr16 = [inp["params"], inp["momentum"]], [wire]
-    cfg = step.launch_config()
-    run, lds = cfg["xcd_run_tiles"], cfg["lds_bytes"]
     nwg = 2 * torch.cuda.get_device_properties(0).multi_processor_count
     read_b, write_b = n * (4 * len(rd32) + 2 * len(rd16)), n * 10
-    scratch = torch.empty(1 << 28, dtype=torch.float32, device="cuda")
     fns = {"step": step,
-           "bare_mix": probes.call(rd32, rd16, wr32, wr16, n, it, run, lds),
-           "reads_alone": probes.call(rd32, rd16, [], [], n, it, run, lds),
-           "writes_alone": probes.call([], [], wr32, wr16, n, it, run, lds),
+           "bare_mix": probes.call(rd32, rd16, wr32, wr16, n, waves, 1, lds),
+           "reads_alone": probes.call(rd32, rd16, [], [], n, waves, 1, lds),
+           "writes_alone": probes.call([], [], wr32, wr16, n, waves, 1, lds),
            "phased": probes.phased(rd32, rd16, wr32, wr16, n, it, nwg)}
-    out = {"workgroups": nwg, "read_bytes": read_b, "write_bytes": write_b}
-    for name, fn in fns.items():
-        med, mn = time_cold(torch, fn, reps, scratch)
-        out[name] = {"cold_median_us": med, "cold_min_us": mn, "warm_us": time_warm(torch, fn, reps)}
-        b = read_b if name == "reads_alone" else (write_b if name == "writes_alone" else read_b + write_b)
-        out[name]["cold_GBps"] = b / (med * 1e-6) / 1e9
-    del scratch
+    out = time_both(torch, fns, reps)
+    add_rates(out, read_b, write_b)
     torch.cuda.synchronize()
     out["phased_waits_given_up"] = int(probes.late[0])
     out["separated_bound_cold_us"] = out["reads_alone"]["cold_median_us"] + out["writes_alone"]["cold_median_us"]
+    out.update({"workgroups": nwg, "read_bytes": read_b, "write_bytes": write_b})
     return out
 
 
@@ -365,7 +381,7 @@ def main() -> int:
         ceil = ceiling(torch, probes, w, inp, wire, step, max(5, min(args.steps, 50)))
         print(json.dumps({"workload": f"{w.name}-shaped parameter set", "params": n, "g": w.g, "P": w.P,
                           "ceiling": ceil, "device_copy_GBps": copy_rate(torch, probes),
-                          "peak_GBps": PEAK_HBM_GBPS}), flush=True)
+                          "device_copy_in_pieces_GBps": copy_rate(torch, probes, form=4), "peak_GBps": PEAK_HBM_GBPS}), flush=True)
         return 0
 
     # the timed region: K calls back to back on the stream the kernels run on,
@@ -411,6 +427,7 @@ def main() -> int:
 
     # a plain 1 GiB device copy (the probe library's 16-byte-lane copy kernel), for context
     copy_gbps = copy_rate(torch, probes)
+    piece_copy_gbps = copy_rate(torch, probes, form=4)
 
     # the separate entry points on the same workload, for context, timed as the
     # step is: calls back to back between one pair of events, so that the host's
@@ -528,6 +545,7 @@ def main() -> int:
                      # the resnet50-shaped target (80% of peak) is stated for the cold figure
                      "target": {"figure": "cold_frac", "frac": 0.80, "met": cold_frac >= 0.80},
                      "device_copy_GBps": copy_gbps,
+                     "device_copy_in_pieces_GBps": piece_copy_gbps,
                      # the step's rate against a plain one-read one-write copy on the same box
                      "frac_of_copy": achieved / copy_gbps,
                      "ceiling": ceil},

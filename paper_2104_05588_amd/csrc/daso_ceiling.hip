@@ -1,12 +1,13 @@
 // Bandwidth ceilings of the fused step's memory access pattern, for the bench
 // only (a library of its own, outside the C ABI of include/daso.h).
 //
-// Each probe kernel makes exactly the loads and stores of a fused step, in the
-// tiles and tile order that daso_fused_launch_config reports (coarser than the
-// step's own split), with the same access widths (16
+// Each probe kernel makes exactly the loads and stores of a fused step, with the
+// same access widths (16
 // bytes per lane for fp32 streams, 8 for bf16) and non-temporal hints, and none
 // of its arithmetic: R32 fp32 and R16 bf16 streams read, W32 fp32 and W16 bf16
-// streams written.  Taking the reads alone, the writes alone and both mixed,
+// streams written.  The piece probes deal the elements to workgroups as the step does
+// (daso_plan.h); the tile probes take them in tiles and runs of tiles per XCD, as
+// daso_fused_launch_config reports.  Taking the reads alone, the writes alone and both mixed,
 // they measure what the step's access mix can reach on a given part; a one-
 // stream copy gives the plain copy rate.  Two more mixed probes take bf16 at 16
 // bytes per lane, to price the wider bf16 access, and a phased probe separates
@@ -15,11 +16,14 @@
 // Safety: every stream holds at least n elements and n is a multiple of 4, of 8
 // for the 16-byte bf16 probes (checked by daso_probe_run before any launch), so a
 // thread touches the vector at element e0 only when e0 < n, which keeps the
-// whole vector inside every buffer.  The grid is at most the tile count of the
-// probe's own tile size, each workgroup looping over tiles grid apart, so every
-// tile is visited once.
+// whole vector inside every buffer.  The grid of a tile probe is at most the tile count of
+// its own tile size, each workgroup looping over tiles grid apart, so every
+// tile is visited once; that of a piece probe has the 8 workgroups of each superblock, in
+// rows of 2^20.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "daso_launch.h"
 
@@ -105,6 +109,42 @@ __global__ __launch_bounds__(kProbeBlock) void probe_kernel(const ProbeArgs a) {
         if (a.sink_flag) a.sink[0] = v.x ^ v.y ^ v.z ^ v.w;
       }
     }
+  }
+}
+
+// The same loads and stores in the step's own split: workgroup w of WAVES wavefronts has
+// piece (wave * 8 + w % 8) of superblock w / 8 for each of them.
+template <int R32, int R16, int W32, int W16, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void piece_kernel(const ProbeArgs a) {
+  const int64_t w = (int64_t(blockIdx.y) << daso::kRowShift) + blockIdx.x;
+  const int64_t sbase = (w >> 3) << daso::super_shift(WAVES);
+  const int64_t e0 = sbase + (int64_t(threadIdx.x >> 6) * 8 + (w & 7)) * daso::kPiece + int64_t(threadIdx.x & 63) * daso::kVec;
+  if (e0 >= a.n) return;
+  u32x4 r32[R32 > 0 ? R32 : 1];
+  u32x2 r16[R16 > 0 ? R16 : 1];
+#pragma unroll
+  for (int s = 0; s < R32; ++s) r32[s] = __builtin_nontemporal_load(static_cast<const u32x4*>(a.rd32[s]) + e0 / 4);
+#pragma unroll
+  for (int s = 0; s < R16; ++s) r16[s] = __builtin_nontemporal_load(static_cast<const u32x2*>(a.rd16[s]) + e0 / 4);
+  u32x4 v = {static_cast<uint32_t>(e0), 1u, 2u, 3u};
+#pragma unroll
+  for (int s = 0; s < R32; ++s) v ^= r32[s];
+#pragma unroll
+  for (int s = 0; s < R16; ++s) {
+    v.x ^= r16[s].x;
+    v.y ^= r16[s].y;
+  }
+#pragma unroll
+  for (int s = 0; s < W32; ++s) __builtin_nontemporal_store(v, static_cast<u32x4*>(a.wr32[s]) + e0 / 4);
+#pragma unroll
+  for (int s = 0; s < W16; ++s) {
+    const u32x2 h = {v.x, v.y};
+    __builtin_nontemporal_store(h, static_cast<u32x2*>(a.wr16[s]) + e0 / 4);
+  }
+  if constexpr (W32 + W16 == 0) {
+    // the fold is needed before the branch, or the loads would move behind it
+    asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+    if (a.sink_flag) a.sink[0] = v.x ^ v.y ^ v.z ^ v.w;
   }
 }
 
@@ -274,7 +314,13 @@ template <int R32, int R16, int W32, int W16, int ITERS>
 hipError_t launch(const ProbeArgs& a, uint32_t grid, uint32_t lds, hipStream_t stream) {
   void* args[] = {const_cast<ProbeArgs*>(&a)};
   const void* k;
-  if constexpr (ITERS == 0)
+  if constexpr (ITERS >= 4) {
+    const int64_t slices = 8 * daso::superblocks(0, a.n, daso::super_shift(ITERS));
+    const int64_t row = std::min(slices, int64_t(1) << daso::kRowShift);
+    return hipLaunchKernel(reinterpret_cast<const void*>(&piece_kernel<R32, R16, W32, W16, ITERS>),
+                           dim3(static_cast<uint32_t>(row), static_cast<uint32_t>((slices + row - 1) / row)),
+                           dim3(64 * ITERS), args, lds, stream);
+  } else if constexpr (ITERS == 0)
     k = reinterpret_cast<const void*>(&probe_wide_kernel<R32, R16, W32, W16, true>);
   else if constexpr (ITERS == -1)
     k = reinterpret_cast<const void*>(&probe_wide_kernel<R32, R16, W32, W16, false>);
@@ -284,16 +330,21 @@ hipError_t launch(const ProbeArgs& a, uint32_t grid, uint32_t lds, hipStream_t s
 }
 
 // The access shapes of the fused step on the five workloads (g + 2 fp32 reads,
-// P bf16 reads; params and momentum written in fp32, the wire in bf16; 2048-
-// element tiles up to 8 copies, 1024 beyond), their reads alone and writes
-// alone, and a plain copy.
+// P bf16 reads; params and momentum written in fp32, the wire in bf16), their reads
+// alone and writes alone: in pieces, by the wavefronts per workgroup that the step
+// takes with statistics, and in tiles (2048 elements up to 8 copies, 1024 beyond); and a
+// plain copy.
 #define DASO_PROBE_SHAPES(X)                                                   \
+  X(6, 2, 2, 1, 4) X(6, 2, 0, 0, 4) X(0, 0, 2, 1, 4)                           \
+  X(6, 4, 2, 1, 4) X(6, 4, 0, 0, 4) X(6, 8, 2, 1, 4) X(6, 8, 0, 0, 4)          \
+  X(6, 16, 2, 1, 4) X(6, 16, 0, 0, 4)                                          \
+  X(10, 32, 2, 1, 8) X(10, 32, 0, 0, 8) X(0, 0, 2, 1, 8)                       \
   X(6, 2, 2, 1, 2) X(6, 2, 0, 0, 2) X(0, 0, 2, 1, 2)   /* g=4, P=2  */        \
   X(6, 4, 2, 1, 2) X(6, 4, 0, 0, 2)                    /* g=4, P=4  */        \
   X(6, 8, 2, 1, 2) X(6, 8, 0, 0, 2)                    /* g=4, P=8  */        \
   X(6, 16, 2, 1, 1) X(6, 16, 0, 0, 1) X(0, 0, 2, 1, 1) /* g=4, P=16 */        \
   X(10, 32, 2, 1, 1) X(10, 32, 0, 0, 1)                /* g=8, P=32 */        \
-  X(1, 0, 1, 0, 2)                                     /* copy      */        \
+  X(1, 0, 1, 0, 2) X(1, 0, 1, 0, 4)                    /* copy      */        \
   X(6, 8, 2, 1, 0) X(6, 8, 2, 1, -1)                   /* g=4, P=8, bf16 16 B */
 
 }  // namespace
@@ -304,14 +355,18 @@ extern "C" {
 // of device pointers, each stream at least n elements of 4 or 2 bytes), tiles of
 // 1024 * iters elements (iters 1 or 2, 4-element vectors; iters 0 and -1: the
 // two 16-byte bf16 forms of probe_wide_kernel, SAME and not, on 2048-element
-// tiles, n a multiple of 8) in runs of xcd_run tiles per XCD, each workgroup holding
+// tiles, n a multiple of 8) in runs of xcd_run tiles per XCD, or with iters 4 or 8 the
+// pieces of workgroups of so many wavefronts (xcd_run 1), each workgroup holding
 // lds_bytes of (unused) LDS, which caps how many share a CU, as the step's
 // launches do.  Returns 0, -1 for a shape without an instance or invalid
 // sizes/pointers, -4 when the launch fails.  Nothing is launched on -1.
 int daso_probe_run(const void* const* rd32, int32_t r32, const void* const* rd16, int32_t r16, void* const* wr32,
                    int32_t w32, void* const* wr16, int32_t w16, uint32_t* sink, int64_t n, int32_t iters,
                    int32_t xcd_run, int32_t lds_bytes, hipStream_t stream) {
-  if (n <= 0 || n % 4 != 0 || iters < -1 || iters > 2 || xcd_run < 1 || sink == nullptr) return -1;
+  if (n <= 0 || n % 4 != 0 || iters < -1 || (iters > 2 && iters != 4 && iters != 8) || xcd_run < 1 ||
+      sink == nullptr)
+    return -1;
+  if (iters >= 4 && xcd_run != 1) return -1;
   if (iters <= 0 && n % 8 != 0) return -1;
   if (lds_bytes < 0 || lds_bytes > 160 * 1024) return -1;
   if (r32 < 0 || r32 > kMaxRead || r16 < 0 || r16 > kMaxRead || w32 < 0 || w32 > kMaxWrite || w16 < 0 ||
@@ -334,7 +389,7 @@ int daso_probe_run(const void* const* rd32, int32_t r32, const void* const* rd16
     if (wr16 == nullptr || wr16[i] == nullptr || (reinterpret_cast<uintptr_t>(wr16[i]) & 15u)) return -1;
     a.wr16[i] = wr16[i];
   }
-  const int64_t tile = int64_t(kProbeBlock) * (iters <= 0 ? 8 : 4 * iters);
+  const int64_t tile = int64_t(kProbeBlock) * (iters <= 0 ? 8 : 4 * std::min(iters, 2));
   const int64_t ntiles = (n + tile - 1) / tile;
   if (ntiles > INT32_MAX) return -1;
   a.sink = sink;

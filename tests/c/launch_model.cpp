@@ -326,6 +326,15 @@ static void fixed_array() {
   EXPECT(symbol_bytes.size() == 1);
 }
 
+// The workgroup and LDS that the step's shapes are launched with, as "g P threads lds".
+static void shapes() {
+  for (int g : {4, 8})
+    for (int P : {2, 4, 8, 16, 32}) {
+      EXPECT(run(Call{g, P, even(25557032, 6553600)}, stream_at(0)) == DASO_OK);
+      std::printf("shape %d %d %u %u\n", g, P, last_block, last_lds);
+    }
+}
+
 int main(int argc, char** argv) {
   if (argc != 3) return 2;
   void* lib = dlopen(argv[1], RTLD_NOW | RTLD_LOCAL);
@@ -337,6 +346,7 @@ int main(int argc, char** argv) {
   else if (scenario == "long_table") long_table();
   else if (scenario == "capture") capture();
   else if (scenario == "fixed_array") fixed_array();
+  else if (scenario == "shapes") shapes();
   else return 2;
   if (failures == 0) std::printf("launch model ok: %d step launches, %d statistics passes\n", steps, passes);
   return failures == 0 ? 0 : 1;

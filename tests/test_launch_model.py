@@ -4,12 +4,15 @@ statistics come from its own partials, whatever the table, in every scratch.  No
 import os
 import shutil
 import subprocess
+import sys
 
 import pytest
 
 from paper_2104_05588_amd import build as B
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, ROOT)
+import bench  # noqa: E402
 
 
 @pytest.fixture(scope="module")
@@ -32,6 +35,7 @@ def run(model, scenario):
     res = subprocess.run([model, B.LIB, scenario], capture_output=True, text=True, timeout=300)
     assert res.returncode == 0, res.stderr[-3000:]
     assert "launch model ok" in res.stdout
+    return res.stdout
 
 
 def test_random_tables(model):
@@ -48,3 +52,10 @@ def test_captured_calls_find_room_after_a_warm_up_of_their_size(model):
 
 def test_the_fixed_array_keeps_its_size_whatever_the_call(model):
     run(model, "fixed_array")
+
+
+def test_the_bench_probes_take_the_shape_that_the_library_launches(model):
+    lines = [ln.split() for ln in run(model, "shapes").splitlines() if ln.startswith("shape")]
+    assert len(lines) == 10
+    for _, g, P, threads, lds in lines:
+        assert (int(threads) // 64, int(lds)) == bench.step_split(int(g), int(P)), (g, P)

@@ -2,7 +2,7 @@
 ABI of include/daso.h): its host checks reject bad arguments before anything is
 launched (no GPU needed), and on the GPU every probe writes exactly the
 elements [0, n) of each output stream, with the values its loads imply, and
-nothing past them, in every tile order and occupancy cap the bench uses."""
+nothing past them, in pieces and in every tile order and occupancy cap the bench uses."""
 import ctypes
 import os
 
@@ -58,7 +58,8 @@ def test_probe_library_exports_its_entry(plib):
 
 @pytest.mark.parametrize("bad", [
     dict(n=0), dict(n=-8), dict(n=4098),                     # n not a positive multiple of 4
-    dict(iters=3), dict(iters=-2),                           # no such form
+    dict(iters=3), dict(iters=-2), dict(iters=5), dict(iters=16),  # no such form
+    dict(iters=4, run=2),                                    # pieces have no runs
     dict(iters=0, n=4100), dict(iters=-1, n=4100),           # 16-byte bf16 forms need n % 8 == 0
     dict(run=0), dict(lds=-1), dict(lds=160 * 1024 + 1),
     dict(sink=None),
@@ -123,7 +124,7 @@ def _expect(form, r32, r16, w32, w16, X32, X16, n):
     X16w = [x.view(np.uint32) for x in X16]
     x32 = np.bitwise_xor.reduce(np.stack(X32), axis=0) if r32 else np.zeros(len(X32[0]) if X32 else n, np.uint32)
     x16 = np.bitwise_xor.reduce(np.stack(X16w), axis=0) if r16 else np.zeros(n // 2 + 4, np.uint32)
-    if form in (1, 2):
+    if form in (1, 2, 4, 8):
         e0 = np.arange(0, n, 4, dtype=np.int64)
         v = np.stack([e0.astype(np.uint32), np.full_like(e0, 1, np.uint32), np.full_like(e0, 2, np.uint32),
                       np.full_like(e0, 3, np.uint32)], axis=1)
@@ -162,6 +163,8 @@ CASES = [  # (r32, r16, w32, w16, form, n)
     (6, 8, 2, 1, 2, 4), (6, 8, 2, 1, 2, 2052), (6, 8, 2, 1, 2, 3 * 2048 + 4), (6, 8, 2, 1, 2, 65536 + 1028),
     (6, 16, 2, 1, 1, 1028), (6, 16, 2, 1, 1, 5 * 1024 + 12),
     (0, 0, 2, 1, 2, 3 * 2048 + 4), (1, 0, 1, 0, 2, 65536 + 12), (6, 8, 0, 0, 2, 2052),
+    (6, 8, 2, 1, 4, 4), (6, 8, 2, 1, 4, 8192), (6, 8, 2, 1, 4, 8196), (6, 16, 2, 1, 4, 3 * 8192 - 4), (0, 0, 2, 1, 4, 2052),
+    (1, 0, 1, 0, 4, 65536 + 12), (6, 8, 0, 0, 4, 8196), (10, 32, 2, 1, 8, 16384 + 260), (0, 0, 2, 1, 8, 4),
     (6, 8, 2, 1, 0, 8), (6, 8, 2, 1, 0, 2056), (6, 8, 2, 1, 0, 65536 + 1032),
     (6, 8, 2, 1, -1, 8), (6, 8, 2, 1, -1, 1032), (6, 8, 2, 1, -1, 2056), (6, 8, 2, 1, -1, 65536 + 1032),
 ]
@@ -175,6 +178,8 @@ def test_probe_writes_exactly_its_elements(plib, case, run, lds):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     r32, r16, w32, w16, form, n = case
+    if form >= 4:
+        run = 1
     print(f"\n[case] probe {case} run={run} lds={lds}", flush=True)
     rng = np.random.default_rng(n * 7 + form + 3)
     X32 = [rng.integers(0, 2**32, n + GUARD, dtype=np.uint64).astype(np.uint32) for _ in range(r32)]
