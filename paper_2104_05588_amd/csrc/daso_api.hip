@@ -199,10 +199,11 @@ int64_t small_average_of(bool with_stats, const daso::Shape& shape) {
 //  - workgroups of eight: 1.
 //  - workgroups of four, without: 1 (g = 8, P = 32: 473 us against 499 with 2).
 //  - the pack (B = 4) needs the whole chip (24 us; 32 us with 16 wavefronts per CU).
-// A launch of up to 3M elements is not capped: it is over before the front has
+// A call of up to 3M elements is not capped: its launch is over before the front has
 // spread, and a cap leaves it in more rounds than need be (g = 4, P = 8 without statistics,
 // capped and not: 0.5M elements 6.1 and 5.5 us, 1M 11.5 and 10.5, 2M 18.3 and 17.6, 4M
-// 34.3 and 34.0, 8M 63.9 and 66.4).
+// 34.3 and 34.0, 8M 63.9 and 66.4).  The launches of a longer call are capped whatever
+// their own size.
 // DASO_FUSED_WG_PER_CU replaces the count for the fused step (0: no cap).
 constexpr int64_t kUncapped = int64_t(3) << 20;
 int32_t lds_of(daso::Mode mode, bool with_stats, const daso::Shape& shape, const StepArgs& a, int64_t elems) {

@@ -161,8 +161,9 @@ struct AccT {
 using Acc = AccT<uint32_t>;
 using Acc64 = AccT<uint64_t>;
 
-// The squares of binary32 values are exact in binary64, so the fused
-// multiply-add rounds as a multiplication and an addition would.
+// The square of a binary32 value is exact in binary64, so for the gradients the fused
+// multiply-add rounds as a multiplication and an addition would; the difference of two has up
+// to 53 bits, and its square is added with one rounding instead of two.
 __device__ __forceinline__ void accumulate(Acc& acc, f32x4 gbar, f32x4 xl, f32x4 xn, unsigned mask, bool nonfinite) {
 #pragma unroll
   for (int k = 0; k < kVec; ++k) {

@@ -13,11 +13,11 @@ namespace daso {
 constexpr int kStatsBlock = 1024;  // threads of stats_kernel
 constexpr int kRowShift = 20;      // at most 2^20 workgroups in a row of a launch's grid
 
-// Occupancy.  A wavefront has all its loads in flight at once, and every kernel here runs
-// fastest with about 60 to 100 KB of them per CU: more of them only
-// spread the front over more DRAM pages.  Each workgroup therefore holds LDS that
-// it does not use, which caps how many share a CU (lds_of in daso_api.hip
-// states the rule).
+// Occupancy.  A wavefront has all its loads in flight at once, and beyond some number of them
+// per CU more only spread the front over more DRAM pages: by instance 50 to 110 KB for
+// workgroups of one wavefront, 50 to 160 KB for those of four, 180 to 260 KB for those of
+// eight.  Each workgroup therefore holds LDS that it does not use, which caps how many share
+// a CU (lds_of in daso_api.hip states the rule, with the counts on either side).
 constexpr int32_t kCuLdsBytes = 160 * 1024;  // LDS per CU on gfx950
 
 // LDS per workgroup that lets at most k workgroups share a CU: a 1 KB margin
