@@ -184,7 +184,10 @@ int64_t small_average_of(bool with_stats, const daso::Shape& shape) {
 //    averages and merges, 5 to 16.  g = 1, P = 0 (B = 12): 87 us at 16, 92 at 8; g = 4, P = 0
 //    (24): 132 at 8, 135 at 12, 145 at 20; g = 4, P = 8 (40): 197 at 5, 200 at 10, 213 at 20;
 //    g = 8, P = 8 (56): 266 at 5, 278 at 10.  Averages of 3, 4 and 8 gradients: best
-//    at 16, 16 and 8; merges of 4, 8 and 16 copies at 16, 12 and 8.
+//    at 16, 16 and 8; merges of 4, 8 and 16 copies at 16, 12 and 8.  Averages and merges of
+//    up to 8 bytes are not capped: 16 such workgroups have too little in flight (averages
+//    of 1 and 2 gradients 31.3 and 46.4 us, 36.1 and 48.0 at 16; merges of 1 and 2 copies
+//    41.4 and 46.4, 47.9 and 53.1; the mean of 1 to 4 copies 29 to 47, 44 to 54).
 //  - the same with bounded counts, whose loads wait for more branches: 300 / B, 6 to 16,
 //    5 beyond B = 80 (g = 3, P = 5, B = 30: 157 us at 10, 164 at 8, 187 at 6; g = 8, P = 12,
 //    64: 297 at 6, 305 at 5 and 8; g = 8 with 12 fp32 copies, 88: 416 at 5, 427 at 6).
@@ -193,8 +196,9 @@ int64_t small_average_of(bool with_stats, const daso::Shape& shape) {
 //    400, 413 at 10, 438 at 16; g = 4 with 40 fp32 copies: 825, 853 and 905).
 //  - workgroups of four, with statistics: 4 up to B = 12 (92 us; 95 with 3), 3 up to
 //    36 (g = 4, P = 4: 177 us; 186 with 2, 180 with 4), else 2 (g = 8, P = 0: 204;
-//    219 with 3); unbounded counts as above 3 (478 us; 522 with 2, 501 with 4) or
-//    2 (425; 444 with 3), and 1 beyond B = 128 (g = 8 with 32 fp32 copies: 745; 817 with
+//    219 with 3); with bounded counts 4 up to 22 (g = P = 1: 106 us, 118 with 3; g = 2, P = 3:
+//    133 and 136; g = 3, P = 2, B = 24: 141 and 139); unbounded counts as above 3 (478 us;
+//    522 with 2, 501 with 4) or 2 (425; 444 with 3), and 1 beyond B = 128 (g = 8 with 32 fp32 copies: 745; 817 with
 //    2; registers hold P = 64 there by themselves).
 //  - workgroups of eight: 1.
 //  - workgroups of four, without: 1 (g = 8, P = 32: 473 us against 499 with 2).
@@ -219,13 +223,14 @@ int32_t lds_of(daso::Mode mode, bool with_stats, const daso::Shape& shape, const
   const bool mostly_bf16 = !a.xf32 && a.P > a.g;
   const auto share = [bytes](int32_t of, int32_t least) { return std::min(16, std::max(least, (of + bytes / 2) / bytes)); };
   int32_t per_cu = 1;
+  if (mode != daso::kModeFused && bytes <= 8) return 0;
   if (shape.waves == 1) {
     if (unbounded) per_cu = mostly_bf16 ? 10 : 7;
     else if (shape.counts == daso::Counts::kBounded) per_cu = share(300, bytes > 80 ? 5 : 6);
     else per_cu = share(mode == daso::kModeFused ? 190 : 240, 5);
   } else if (with_stats && shape.waves == 4) {
     if (unbounded) per_cu = mostly_bf16 ? 3 : 2;
-    else per_cu = bytes <= 12 ? 4 : bytes <= 36 ? 3 : bytes <= 128 ? 2 : 1;
+    else per_cu = bytes <= (shape.counts == daso::Counts::kBounded ? 22 : 12) ? 4 : bytes <= 36 ? 3 : bytes <= 128 ? 2 : 1;
   }
   return daso::lds_for_workgroups_per_cu(per_cu);
 }
