@@ -201,7 +201,8 @@ int64_t small_average_of(bool with_stats, const daso::Shape& shape) {
 //    522 with 2, 501 with 4) or 2 (425; 444 with 3), and 1 beyond B = 128 (g = 8 with 32 fp32 copies: 745; 817 with
 //    2; registers hold P = 64 there by themselves).
 //  - workgroups of eight: 1.
-//  - workgroups of four, without: 1 (g = 8, P = 32: 473 us against 499 with 2).
+//  - workgroups of four, without: 1 (g = 8, P = 32: 473 us against 499 with 2); for the merge
+//    of 32 bf16 copies 3 (289; 298 with 2, 341 with 1), for their mean 2 (263; 270 with 3).
 //  - the pack (B = 4) needs the whole chip (24 us; 32 us with 16 wavefronts per CU).
 // A call of up to 3M elements is not capped: its launch is over before the front has
 // spread, and a cap leaves it in more rounds than need be (g = 4, P = 8 without statistics,
@@ -231,6 +232,8 @@ int32_t lds_of(daso::Mode mode, bool with_stats, const daso::Shape& shape, const
   } else if (with_stats && shape.waves == 4) {
     if (unbounded) per_cu = mostly_bf16 ? 3 : 2;
     else per_cu = bytes <= (shape.counts == daso::Counts::kBounded ? 22 : 12) ? 4 : bytes <= 36 ? 3 : bytes <= 128 ? 2 : 1;
+  } else if (mode != daso::kModeFused && !a.xf32) {
+    per_cu = mode == daso::kModeMean ? 2 : 3;
   }
   return daso::lds_for_workgroups_per_cu(per_cu);
 }

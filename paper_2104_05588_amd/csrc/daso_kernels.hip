@@ -476,15 +476,17 @@ constexpr Counts counts_of() {
 // Without them one, so that a place on a CU is free again as soon as its own loads and
 // stores are done (resnet50-shaped 196 against 204 us, the average of 8 gradients
 // 140 against 145, g = 8 with 12 fp32 copies 406 against 437), except for exact
-// counts that take 88 bytes per element or more: there 4 wavefronts on one CU run 1 to 6%
-// faster than 4 spread over the chip (g = 8, P = 32: 473 against 486 us).
+// counts that take 88 bytes per element or more, or merges of 32 bf16 copies: there 4
+// wavefronts on one CU run 1 to 9% faster than 4 spread over the chip (g = 8, P = 32: 473
+// against 486 us; the merge 289 against 300 at best, the mean 263 against 282).
 template <int MODE, int G, int PP, bool STATS, bool XF>
 constexpr int waves_of() {
   using V = VecIn<MODE, G, PP, XF>;
   constexpr int bytes = 4 * V::kG + (XF ? 4 : 2) * V::kP + (MODE == kModeFused ? 8 : reads_x(MODE) ? 4 : 0);
   constexpr bool heavy = counts_of<MODE, G, PP>() == Counts::kExact && bytes >= 88;
+  constexpr bool heavy_merge = MODE != kModeFused && !XF && V::kP >= 32 && counts_of<MODE, G, PP>() == Counts::kExact;
   if (STATS) return heavy && bytes <= 128 ? 8 : 4;
-  return heavy ? 4 : 1;
+  return heavy || heavy_merge ? 4 : 1;
 }
 
 // ------------------------------------------------- unbounded run-time counts
