@@ -510,7 +510,9 @@ __device__ __forceinline__ V get(const T* p, int64_t base, uint32_t off, unsigne
 
 // Whether a piece's gradients and copies may be read as whole vectors whatever elements are
 // selected: none of the vectors reaches past the buffers' n elements, and no gradient is
-// being overwritten with the average.
+// being overwritten with the average.  Four loads in place of one for every stream of a cut
+// piece are the longest chain of a short call (g = 9, P = 40, 30,000 parameters in two buckets
+// without statistics 18.6 us, with whole vectors 10.7; 25.6M parameters 581 and 577).
 __device__ __forceinline__ bool whole_reads(const StepArgs& a, int64_t base) {
   return a.in_place_avg == 0 && (base + kPiece <= a.n || (a.n & (kVec - 1)) == 0);
 }
@@ -751,7 +753,7 @@ __global__ __launch_bounds__((64 * waves_of<MODE, G, PP, STATS, XF>())) void ste
       const unsigned mask = vec_mask(base + off, a.start[b], a.start[b + 1]);
       if (mask) {
         if constexpr (kBatched) finish<MODE, G, PP, XF, STATS, false>(a, base, off, mask, v, two_s, qg, qm, acc);
-        else if (kStats && whole_reads(a, base)) step_any<MODE, STATS, XF, Lanes::kRead>(a, base, off, mask, two_s, qg, qm, acc);
+        else if (whole_reads(a, base)) step_any<MODE, STATS, XF, Lanes::kRead>(a, base, off, mask, two_s, qg, qm, acc);
         else step_any<MODE, STATS, XF, Lanes::kCut>(a, base, off, mask, two_s, qg, qm, acc);
       }
       if constexpr (kStats) {

@@ -151,7 +151,7 @@ def test_launches_of_small_buckets(g, P, f32, stats):
     theirs as they are."""
     rng = np.random.default_rng(31 * g + P + stats)
     for sizes in ([1] * 300, list(range(0, 130)) * 2, [128, 0] * 65, [129, 1, 1, 1], [2, 1], [64] * 9, [65] * 9,
-                  [2048, 0, 1] * 45, [2049, 1, 1], [4096, 1, 0] * 3, [4097, 1, 1], [8192, 3, 5], [8193, 1, 1, 255],
+                  [2048, 0, 1] * 45, [2049, 1, 1], [4096, 1, 0] * 3, [4097, 1, 1], [6144, 3, 5], [6145, 1, 1, 255], [3072, 3072, 3073],
                   [40] * 128 + [15000, 7] + [3] * 126 + [257, 1] * 64, [30] * 127 + [9001] + [30] * 200,
                   [9000, 5, 700, 3, 9000, 4], [9000, 5, 700, 3, 9000, 1, 2]):
         bks, pos = [], 0
