@@ -210,7 +210,6 @@ int64_t small_average_of(bool with_stats, const daso::Shape& shape) {
 // 34.3 and 34.0, 8M 63.9 and 66.4).  The launches of a longer call are capped whatever
 // their own size.
 // DASO_FUSED_WG_PER_CU replaces the count for the fused step (0: no cap).
-constexpr int64_t kUncapped = int64_t(3) << 20;
 int32_t lds_of(daso::Mode mode, bool with_stats, const daso::Shape& shape, const StepArgs& a, int64_t elems) {
   if (mode == daso::kModePack) return 0;
   const int64_t over = fused_cap_override();
@@ -219,7 +218,7 @@ int32_t lds_of(daso::Mode mode, bool with_stats, const daso::Shape& shape, const
   if (mode == daso::kModeAvg) bytes = 4 * a.g;
   if (mode == daso::kModeMerge) bytes += 4;
   if (mode == daso::kModeFused) bytes += 4 * a.g + 8;
-  if (elems <= kUncapped) return 0;
+  if (elems <= daso::kShortCall) return 0;
   const bool unbounded = shape.counts == daso::Counts::kUnbounded;
   const bool mostly_bf16 = !a.xf32 && a.P > a.g;
   const auto share = [bytes](int32_t of, int32_t least) { return std::min(16, std::max(least, (of + bytes / 2) / bytes)); };

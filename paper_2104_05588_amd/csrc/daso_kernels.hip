@@ -479,14 +479,30 @@ constexpr Counts counts_of() {
 // counts that take 88 bytes per element or more, or merges of 32 bf16 copies: there 4
 // wavefronts on one CU run 1 to 9% faster than 4 spread over the chip (g = 8, P = 32: 473
 // against 486 us; the merge 289 against 300 at best, the mean 263 against 282).
-template <int MODE, int G, int PP, bool STATS, bool XF>
-constexpr int waves_of() {
+template <int MODE, int G, int PP, bool XF>
+constexpr bool heavy() {
   using V = VecIn<MODE, G, PP, XF>;
   constexpr int bytes = 4 * V::kG + (XF ? 4 : 2) * V::kP + (MODE == kModeFused ? 8 : reads_x(MODE) ? 4 : 0);
-  constexpr bool heavy = counts_of<MODE, G, PP>() == Counts::kExact && bytes >= 88;
-  constexpr bool heavy_merge = MODE != kModeFused && !XF && V::kP >= 32 && counts_of<MODE, G, PP>() == Counts::kExact;
-  if (STATS) return heavy && bytes <= 128 ? 8 : 4;
-  return heavy || heavy_merge ? 4 : 1;
+  constexpr bool merge32 = MODE != kModeFused && !XF && V::kP >= 32;
+  return counts_of<MODE, G, PP>() == Counts::kExact && (bytes >= 88 || merge32);
+}
+
+template <int MODE, int G, int PP, bool STATS, bool XF>
+constexpr int waves_of() {
+  constexpr bool is_heavy = heavy<MODE, G, PP, XF>();
+  if (STATS) return is_heavy && 4 * G + (XF ? 4 : 2) * PP + 8 <= 128 ? 8 : 4;
+  return is_heavy ? 4 : 1;
+}
+
+// A short call has few workgroups of eight for the CUs there are: it takes fours (g = 8,
+// P = 32, 131,072 parameters 7.0 us against 7.8, 1M 20.4 and 21.5, 3M 61.7 and 63.7, but 25.6M
+// 497 and 479).  `f` is called with the number of wavefronts per workgroup, a compile-time constant.
+template <int MODE, int G, int PP, bool STATS, bool XF, typename F>
+auto with_waves(const StepArgs& a, const F& f) {
+  constexpr int kWaves = waves_of<MODE, G, PP, STATS, XF>();
+  if constexpr (kWaves == 8)
+    if (a.n <= kShortCall) return f(std::integral_constant<int, 4>{});
+  return f(std::integral_constant<int, kWaves>{});
 }
 
 // ------------------------------------------------- unbounded run-time counts
@@ -687,11 +703,10 @@ __device__ __forceinline__ unsigned vec_mask(int64_t e0, int64_t lo, int64_t hi)
 // looked up first), same buffers in turn: ragged step 82.7 to 78.0 us, many small
 // buckets 712 to 680, resnet50-shaped 216 to 206 (without statistics 213.5 to 196),
 // the average of 8 gradients 444 to 399, merges 5 to 9% faster; boxes differ by a few percent.
-template <int MODE, int G, int PP, bool STATS, bool XF>
-__global__ __launch_bounds__((64 * waves_of<MODE, G, PP, STATS, XF>())) void step_kernel(const StepArgs a) {
+template <int MODE, int G, int PP, bool STATS, bool XF, int kWaves>
+__global__ __launch_bounds__(64 * kWaves) void step_kernel(const StepArgs a) {
   constexpr bool kBatched = batched<MODE, G, PP>();
   constexpr bool kStats = STATS && MODE == kModeFused;
-  constexpr int kWaves = waves_of<MODE, G, PP, STATS, XF>();
   constexpr int kShift = super_shift(kWaves);
   const int64_t w = (int64_t(blockIdx.y) << kRowShift) + blockIdx.x;
   const int wave = kWaves == 1 ? 0 : __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
@@ -925,21 +940,25 @@ struct Launcher {
   template <int MODE, int G, int PP, bool STATS, bool XF>
   hipError_t run() const {
     void* args[] = {const_cast<StepArgs*>(&a)};
-    return hipLaunchKernel(reinterpret_cast<const void*>(&step_kernel<MODE, G, PP, STATS, XF>), grid,
-                           dim3(64 * waves_of<MODE, G, PP, STATS, XF>()), args, lds, stream);
+    return with_waves<MODE, G, PP, STATS, XF>(a, [&](auto waves) {
+      return hipLaunchKernel(reinterpret_cast<const void*>(&step_kernel<MODE, G, PP, STATS, XF, waves()>), grid,
+                             dim3(64 * waves()), args, lds, stream);
+    });
   }
 };
 
 struct ShapeOf {
+  const StepArgs& a;
   template <int MODE, int G, int PP, bool STATS, bool XF>
   Shape run() const {
-    return Shape{waves_of<MODE, G, PP, STATS, XF>(), counts_of<MODE, G, PP>()};
+    return with_waves<MODE, G, PP, STATS, XF>(
+        a, [](auto waves) { return Shape{waves(), counts_of<MODE, G, PP>()}; });
   }
 };
 
 }  // namespace
 
-Shape launch_shape(Mode mode, bool with_stats, const StepArgs& a) { return dispatch(mode, with_stats, a, ShapeOf{}); }
+Shape launch_shape(Mode mode, bool with_stats, const StepArgs& a) { return dispatch(mode, with_stats, a, ShapeOf{a}); }
 
 hipError_t launch_step(Mode mode, bool with_stats, const StepArgs& a, dim3 grid, uint32_t lds, hipStream_t stream) {
   return dispatch(mode, with_stats, a, Launcher{a, grid, lds, stream});

@@ -24,6 +24,10 @@ constexpr int32_t kCuLdsBytes = 160 * 1024;  // LDS per CU on gfx950
 // covers the kernel's own few bytes of LDS and the allocation granule.
 inline int32_t lds_for_workgroups_per_cu(int32_t k) { return k >= 1 ? kCuLdsBytes / k - 1024 : 0; }
 
+// Elements up to which a call is short: its launches are over before the front of their workgroups
+// has spread, so it takes no occupancy cap (lds_of) and no workgroups of eight wavefronts (with_waves).
+constexpr int64_t kShortCall = int64_t(3) << 20;
+
 // An eager fused launch with statistics of at most this many wavefronts (131,072
 // parameters) has its last workgroup sum the statistics (StepArgs::done) instead of
 // a second launch.  The workgroups count themselves done in one counter, at 5 to 11 ns

@@ -235,7 +235,7 @@ static void random_tables() {
   std::mt19937_64 rng(5);
   for (int trial = 0; trial < 300; ++trial) {
     Call c{kShapes[trial % 6].first, kShapes[trial % 6].second, {}};
-    const int64_t n = 1 + static_cast<int64_t>(rng() % (trial % 5 ? 200000 : 3000000));
+    const int64_t n = 1 + static_cast<int64_t>(rng() % (trial % 5 ? 200000 : 5000000));
     int64_t pos = 0;
     while (pos < n) {
       const int64_t size = std::min<int64_t>(n - pos, static_cast<int64_t>(rng() % (1 + n / (1 + static_cast<int64_t>(rng() % 300)))));
@@ -326,12 +326,17 @@ static void fixed_array() {
   EXPECT(symbol_bytes.size() == 1);
 }
 
-// The workgroup and LDS that the step's shapes are launched with, as "g P threads lds".
+// The workgroup and LDS that the step's shapes are launched with, as "g P threads lds", and
+// those of the longest short call and of the shortest beyond.
 static void shapes() {
   for (int g : {4, 8})
     for (int P : {2, 4, 8, 16, 32}) {
       EXPECT(run(Call{g, P, even(25557032, 6553600)}, stream_at(0)) == DASO_OK);
       std::printf("shape %d %d %u %u\n", g, P, last_block, last_lds);
+      for (int64_t n : {daso::kShortCall, daso::kShortCall + 1}) {
+        EXPECT(run(Call{g, P, even(n, n)}, stream_at(0)) == DASO_OK);
+        std::printf("%s %d %d %u %u\n", n > daso::kShortCall ? "shape" : "short", g, P, last_block, last_lds);
+      }
     }
 }
 

@@ -61,6 +61,23 @@ def test_pieces_at_their_edges(g, P, f32, stats):
         compare_fused(got, want, f"pieces g={g} P={P} n={n}", gavg=True, stats=stats)
 
 
+@pytest.mark.parametrize("g,P,f32", [(8, 32, False), (4, 16, True)])
+@pytest.mark.parametrize("n", [3 << 20, (3 << 20) + 1, (3 << 20) + 12_292])
+def test_workgroups_of_eight_begin_beyond_a_short_call(g, P, f32, n):
+    """The longest call in workgroups of four wavefronts, and calls in eights that end in a
+    superblock's first vector and last workgroups, with buckets that meet inside a piece."""
+    rng = np.random.default_rng(n + g)
+    bks = [(0, 300, 2), (300, 1_500_003, 0), (1_500_303, n - 1_500_303, 1)]
+    inp = random_inputs(rng, n, g, P)
+    if f32:
+        inp["stale"] = [O.bf16_widen(s) + F32(1e-6) for s in inp["stale"]]
+    announce("eights g=", g, "P=", P, "f32" if f32 else "bf16", "n=", n)
+    want = O.fused_sync_step(inp["grads"], inp["params"], inp["momentum"], inp["stale"], bks, 0.1, 0.9, 1e-4,
+                             exchange="f32" if f32 else "bf16")
+    got = run_fused(inp, bks, wd=1e-4, gavg="new", stats=True, f32=f32)
+    compare_fused(got, want, f"eights g={g} P={P} n={n}", gavg=True, stats=True)
+
+
 @pytest.mark.parametrize("f32", [False, True])
 @pytest.mark.parametrize("P", [1, 2, 4, 5, 8, 12, 16, 20, 32, 40])
 def test_mean_of_copies_at_its_edges(P, f32):

@@ -56,6 +56,13 @@ def test_the_fixed_array_keeps_its_size_whatever_the_call(model):
 
 def test_the_bench_probes_take_the_shape_that_the_library_launches(model):
     lines = [ln.split() for ln in run(model, "shapes").splitlines() if ln.startswith("shape")]
-    assert len(lines) == 10
+    assert len(lines) == 20
     for _, g, P, threads, lds in lines:
         assert (int(threads) // 64, int(lds)) == bench.step_split(int(g), int(P)), (g, P)
+
+
+def test_short_calls_take_workgroups_of_four_and_no_cap(model):
+    lines = [ln.split() for ln in run(model, "shapes").splitlines() if ln.startswith("short")]
+    assert len(lines) == 10
+    for _, g, P, threads, lds in lines:
+        assert (int(threads), int(lds)) == (256, 0), (g, P)
