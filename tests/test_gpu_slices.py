@@ -61,6 +61,34 @@ def test_pieces_at_their_edges(g, P, f32, stats):
         compare_fused(got, want, f"pieces g={g} P={P} n={n}", gavg=True, stats=stats)
 
 
+@pytest.mark.parametrize("stats", [False, True])
+@pytest.mark.parametrize("g,P,f32", [(8, 32, False), (4, 64, False), (4, 16, True), (8, 32, True)])
+def test_last_pieces_of_whole_vectors(g, P, f32, stats):
+    """Calls that end inside a piece at a multiple of 4, whose last vectors are read whole, with
+    buckets that meet inside a vector and without; and at an odd element, read one by one."""
+    rng = np.random.default_rng(3000 * g + 10 * P + stats)
+    for n in (4, 252, 260, 1028, 8188, 8196, 30_000, 30_001):
+        for bks in ([(0, n, 2)], [(0, n - 4, 1), (n - 4, 4, 0)], [(n - 3, 3, 3), (0, n - 3, 1)]):
+            inp = random_inputs(rng, n, g, P)
+            if f32:
+                inp["stale"] = [O.bf16_widen(s) + F32(1e-6) for s in inp["stale"]]
+            announce("last piece g=", g, "P=", P, "f32" if f32 else "bf16", "stats" if stats else "", "n=", n)
+            want = O.fused_sync_step(inp["grads"], inp["params"], inp["momentum"], inp["stale"], bks, 0.1, 0.9, 1e-4,
+                                     exchange="f32" if f32 else "bf16")
+            got = run_fused(inp, bks, wd=1e-4, gavg="alias", stats=stats, f32=f32)
+            compare_fused(got, want, f"last piece g={g} P={P} n={n}", gavg=True, stats=stats)
+            want, wire = O.global_merge(inp["params"], inp["stale"], bks, pack=True, exchange="f32" if f32 else "bf16")
+            xd = dev_f32(inp["params"])
+            wd = torch.empty(n, dtype=torch.float32 if f32 else torch.int16, device="cuda")
+            daso.global_merge(xd, [(dev_f32 if f32 else dev_bf16)(s) for s in inp["stale"]], bks, wd)
+            torch.cuda.synchronize()
+            check_f32(host_f32(xd), want, f"merge of P={P} n={n}")
+            if f32:
+                check_f32(host_f32(wd), wire, f"wire of P={P} n={n}")
+            else:
+                check_u16(host_u16(wd), wire, f"wire of P={P} n={n}")
+
+
 @pytest.mark.parametrize("g,P,f32", [(8, 32, False), (4, 16, True)])
 @pytest.mark.parametrize("n", [3 << 20, (3 << 20) + 1, (3 << 20) + 12_292])
 def test_workgroups_of_eight_begin_beyond_a_short_call(g, P, f32, n):
