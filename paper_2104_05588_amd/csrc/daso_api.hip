@@ -166,7 +166,7 @@ int64_t fused_cap_override() {
 //    g = 8, P = 32: 350 and 114, 234 and 90; g = 4, P = 64: 254 and 168, 181 and 133; but
 //    4M in buckets of 1500, g = 4, P = 64: 364 and 545; of 3001, g = 4, P = 8: 109 and 166;
 //  - with statistics and unbounded counts, g = 9, P = 40, 4M in buckets of 1501 1036 and 446,
-//    3001 413 and 326, 4096 210 and 304; 8192 elements in two buckets 16.6 and 23.2;
+//    3001 413 and 326, 4096 210 and 304; 8192 elements in two buckets 12.2 and 23.2;
 //  - without, 262144 elements, g = 4, P = 8: 63 elements 251 and 176, 200 60 and 56;
 //    g = 4, P = 64: 462 and 414, 100 229 and 243;
 //  - without, unbounded counts, g = 9, P = 40, 4M in buckets of 1501 420 and 268, 2001 336 and

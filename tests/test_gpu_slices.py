@@ -62,13 +62,19 @@ def test_pieces_at_their_edges(g, P, f32, stats):
 
 
 @pytest.mark.parametrize("stats", [False, True])
-@pytest.mark.parametrize("g,P,f32", [(8, 32, False), (4, 64, False), (4, 16, True), (8, 32, True)])
+@pytest.mark.parametrize("g,P,f32", [(8, 32, False), (4, 64, False), (4, 16, True), (8, 32, True), (9, 3, False),
+                                     (2, 45, False), (4, 33, True)])
 def test_last_pieces_of_whole_vectors(g, P, f32, stats):
     """Calls that end inside a piece at a multiple of 4, whose last vectors are read whole, with
-    buckets that meet inside a vector and without; and at an odd element, read one by one."""
+    buckets that meet inside a vector and without, several of them in one piece, whose vectors
+    unbounded counts then take in one pass; and at an odd element, read one by one."""
     rng = np.random.default_rng(3000 * g + 10 * P + stats)
     for n in (4, 252, 260, 1028, 8188, 8196, 30_000, 30_001):
-        for bks in ([(0, n, 2)], [(0, n - 4, 1), (n - 4, 4, 0)], [(n - 3, 3, 3), (0, n - 3, 1)]):
+        tables = [[(0, n, 2)], [(0, n - 4, 1), (n - 4, 4, 0)], [(n - 3, 3, 3), (0, n - 3, 1)]]
+        if n >= 30_000:
+            cuts = [0, 20_000, 20_004, 20_052, 20_052, 20_152, n]
+            tables.append([(s, e - s, k % 4) for k, (s, e) in enumerate(zip(cuts, cuts[1:]))])
+        for bks in tables:
             inp = random_inputs(rng, n, g, P)
             if f32:
                 inp["stale"] = [O.bf16_widen(s) + F32(1e-6) for s in inp["stale"]]
